@@ -215,6 +215,22 @@ __device__ __forceinline__ bool finite_(T x) {
     return x == x && abs_(x) <= (T)3.0e38;
 }
 
+// finite_ of every component of a state: the largest magnitude, NaN passing through, against
+// the bound (in float half an instruction per component instead of three).
+template <typename T, int M>
+__device__ __forceinline__ bool finite_state(const StateT<T, M>& s) {
+    T m = T(0);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) m = __builtin_elementwise_maximum(m, abs_(s.p[j]));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) m = __builtin_elementwise_maximum(m, abs_(s.q[j]));
+#pragma unroll
+    for (int j = 0; j < 6; ++j) m = __builtin_elementwise_maximum(m, abs_(s.nu[j]));
+#pragma unroll
+    for (int i = 0; i < M; ++i) m = __builtin_elementwise_maximum(m, abs_(s.n[i]));
+    return m <= (T)3.0e38;
+}
+
 __device__ __forceinline__ bool is_max_slot(int j) {
     return j == kStMaxSpeed || j == kStMaxRate || j == kStMaxDrift;
 }
@@ -393,7 +409,7 @@ template <typename T, int M>
 __device__ __forceinline__ void renorm_attitude(StateT<T, M>& s, float st[kStats]) {
     T n2 = fma_(s.q[3], s.q[3], fma_(s.q[2], s.q[2], fma_(s.q[1], s.q[1], s.q[0] * s.q[0])));
     T drift = abs_(n2 - T(1));
-    if (drift > T(1e-6)) {
+    if (__builtin_expect(drift > T(1e-6), 0)) {
         double qd[4] = {(double)s.q[0], (double)s.q[1], (double)s.q[2], (double)s.q[3]};
         double inv = 1.0 / sqrt(qd[0] * qd[0] + qd[1] * qd[1] + qd[2] * qd[2] + qd[3] * qd[3]);
 #pragma unroll

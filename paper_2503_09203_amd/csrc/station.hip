@@ -221,23 +221,28 @@ __device__ __forceinline__ void restart_spread(const StationConsts& P, uint64_t 
 // in registers from step to step, the next command row is fetched during the current step,
 // and each step's observation, reward and flags go to their own output row. kMulti = false
 // is the one-step form (a Gym step), compiled without the loop.
+//
+// Vector memory operations complete in the order they were issued, so a wait for a load also
+// waits for every store before it. A step issues the next row's loads first and its 22 or
+// more stores last, and takes the loaded row at its end: the wait then covers the stores of
+// the step before (a whole step old) and not the ones just issued. Taken at the top of the
+// next step, behind the loop's back edge, the compiler could not count the stores and waited
+// for all of them, a full write latency in every step (2.34 us per step at 65,536
+// environments in calls of 100, 1.87 since). For the same reason every store is unconditional: the block
+// size divides the padded segment (launch_station), so no lane lies past it.
 template <typename T, int M, bool kShaped, bool kFins, bool kPayload, bool kMulti>
 __global__ void __launch_bounds__(256) k_station_step(StationLaunch<T> L) {
     const StationArgs<T>& A = L.a;
     const int64_t env = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t np = A.npad;
-    // Every lane loads everything, with no branch ahead of its loads: lanes past the segment
-    // (whole waves) at its last slot, padding slots as they are (they hold a valid state,
-    // parameter set and command). Behind a branch on the kernel arguments, each group of
-    // loads waited for another argument fetch; a one-step launch took about 8 us.
-    // Every lane also takes the steps (the commands' loads otherwise moved behind the branch
-    // that left padding lanes out): padding lanes store and report nothing and never end an
-    // episode (they stay in the wave for the restarts); lanes past the segment write nothing.
-    const bool live = env < np;
+    // Every lane loads everything and takes the steps, with no branch ahead of its loads:
+    // behind a branch on the kernel arguments, each group of loads waited for another
+    // argument fetch; a one-step launch took about 8 us. Padding lanes (they hold a valid
+    // state, parameter set and command) report zeros, store no state and never end an episode
+    // (they stay in the wave for the restarts).
     const bool valid = env < A.nvalid;
-    const int64_t el = live ? env : np - 1;
     StateT<T, M> s;
-    load_state<T, M>(A.state, np, el, s);
+    load_state<T, M>(A.state, np, env, s);
     // classes with fins carry the attitude's low-order words through the launch (float)
     constexpr bool kComp = kFins && std::is_same<T, float>::value;
     StateLo<T> lo;
@@ -245,68 +250,57 @@ __global__ void __launch_bounds__(256) k_station_step(StationLaunch<T> L) {
     for (int j = 0; j < 4; ++j) lo.q[j] = T(0);
     T tg[7];
 #pragma unroll
-    for (int j = 0; j < 7; ++j) tg[j] = A.tgt[j * np + el];
+    for (int j = 0; j < 7; ++j) tg[j] = A.tgt[j * np + env];
     const ClassT<T> C = class_in_vgpr<T, M, kFins>(L.cls);
     EnvT<T> E;
     T IA2[3], Brb[3];
     bool restarted = false;
-    T nxt[M];
-    load_record<T, kPayload>(A.rec, np, el, C.flags, E);
-    int32_t ep = A.ep[el];
-    int32_t et = A.et[el];
+    T a[M], nxt[M];
+    load_record<T, kPayload>(A.rec, np, env, C.flags, E);
+    int32_t ep = A.ep[env];
+    int32_t et = A.et[env];
 #pragma unroll
-    for (int i = 0; i < M; ++i) nxt[i] = A.act[i * np + el];
+    for (int i = 0; i < M; ++i) nxt[i] = A.act[i * np + env];
     env_prologue<T, kPayload>(C, E, IA2, Brb);
     const int32_t n_steps = kMulti ? A.n_steps : 1;
+    // drained before the loop: a wait left to the values' first use would sit in the loop
+    if constexpr (kMulti) __builtin_amdgcn_s_waitcnt(0);
+#pragma unroll
+    for (int i = 0; i < M; ++i) a[i] = clip1(nxt[i]);
     for (int32_t k = 0; k < n_steps; ++k) {
-        T r = T(0);
-        bool term = false, trunc = false;
-        {
-            T a[M];
+        if constexpr (kMulti) {
+            // the next row, clamped to the last (a load guarded per step would make the
+            // compiler wait for it before the step)
+            const T* an = A.act + (int64_t)(k + 1 < n_steps ? k + 1 : k) * A.act_stride + env;
 #pragma unroll
-            for (int i = 0; i < M; ++i) a[i] = clip1(nxt[i]);
-            if constexpr (kMulti) {
-                // the next row, clamped to the last (a load guarded per step would make the
-                // compiler wait for it before the step)
-                const T* an = A.act + (int64_t)(k + 1 < n_steps ? k + 1 : k) * A.act_stride + el;
-#pragma unroll
-                for (int i = 0; i < M; ++i) nxt[i] = an[i * np];
-            }
-            // substeps >= 1 (checked at creation): the first step is unconditional, so no
-            // branch on the argument stands between the record's loads and their use
-            int j = 0;
-            do {
-                step_body<T, M, false, kShaped, kFins, kPayload, kComp>(C, E, IA2, Brb, s, a, nullptr, &lo);
-            } while (++j < A.P.substeps);
-            float st[kStats];  // launch statistics are not kept by the task
-            renorm_attitude<T, M>(s, st);
-
-            // reward and termination on the state the transition ends in
-            bool fin = true;
-#pragma unroll
-            for (int j = 0; j < 3; ++j) fin &= finite_(s.p[j]);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) fin &= finite_(s.q[j]);
-#pragma unroll
-            for (int j = 0; j < 6; ++j) fin &= finite_(s.nu[j]);
-#pragma unroll
-            for (int i = 0; i < M; ++i) fin &= finite_(s.n[i]);
-            const T d0 = tg[0] - s.p[0], d1 = tg[1] - s.p[1], d2 = tg[2] - s.p[2];
-            const T d = sqrt_(d0 * d0 + d1 * d1 + d2 * d2);
-            T e[4];
-            attitude_error(s.q, tg + 3, e);
-            T a2 = T(0);
-#pragma unroll
-            for (int i = 0; i < M; ++i) a2 += a[i] * a[i];
-            const T up = T(1) - T(2) * (s.q[1] * s.q[1] + s.q[2] * s.q[2]);
-            r = exp_(-d * (T)A.P.inv_sigma) - (T)A.P.w_att * (T(1) - e[0] * e[0]) - (T)A.P.w_act_m * a2;
-            term = valid && (!fin || d > (T)A.P.d_max || up < (T)A.P.cos_tilt);
-            if (!fin || !valid) r = T(0);
-            et += valid ? 1 : 0;
-            trunc = valid && et >= A.P.max_steps;
+            for (int i = 0; i < M; ++i) nxt[i] = an[i * np];
         }
+        // substeps >= 1 (checked at creation): the first step is unconditional, so no
+        // branch on the argument stands between the record's loads and their use
+        int j = 0;
+        do {
+            step_body<T, M, false, kShaped, kFins, kPayload, kComp>(C, E, IA2, Brb, s, a, nullptr, &lo);
+        } while (++j < A.P.substeps);
+        float st[kStats];  // launch statistics are not kept by the task
+        renorm_attitude<T, M>(s, st);
+
+        // reward and termination on the state the transition ends in
+        const bool fin = finite_state<T, M>(s);
+        const T d0 = tg[0] - s.p[0], d1 = tg[1] - s.p[1], d2 = tg[2] - s.p[2];
+        const T d = sqrt_(d0 * d0 + d1 * d1 + d2 * d2);
+        T e[4];
+        attitude_error(s.q, tg + 3, e);
+        T a2 = T(0);
+#pragma unroll
+        for (int i = 0; i < M; ++i) a2 += a[i] * a[i];
+        const T up = T(1) - T(2) * (s.q[1] * s.q[1] + s.q[2] * s.q[2]);
+        T r = exp_(-d * (T)A.P.inv_sigma) - (T)A.P.w_att * (T(1) - e[0] * e[0]) - (T)A.P.w_act_m * a2;
+        const bool term = valid && (!fin || d > (T)A.P.d_max || up < (T)A.P.cos_tilt);
+        if (!fin || !valid) r = T(0);
+        et += valid ? 1 : 0;
+        const bool trunc = valid && et >= A.P.max_steps;
         const bool done = term || trunc;
-        if (done) {
+        if (__builtin_expect(done, 0)) {
             if (A.final_obs) write_obs<T, M>(A.final_obs + (int64_t)k * A.obs_stride, np, env, s, tg);
             ++ep;
             et = 0;
@@ -315,18 +309,22 @@ __global__ void __launch_bounds__(256) k_station_step(StationLaunch<T> L) {
             for (int j = 0; j < 4; ++j) lo.q[j] = T(0);
         }
         const uint64_t need = __ballot(done);
-        if (need) {
+        // rare: weighed as likely, the restart's constants crowd the step's out of the scalar
+        // registers
+        if (__builtin_expect(need != 0, 0)) {
             if (__popcll(need) <= kSpreadRestarts)
                 restart_spread<T, M>(A.P, need, (uint32_t)(A.env_off + env), (uint32_t)ep, s, tg);
             else if (done)
                 start_state<T, M>(A.P, (uint64_t)(A.env_off + env), (uint32_t)ep, s, tg);
         }
-        if (live) {
-            write_obs<T, M>(A.obs + (int64_t)k * A.obs_stride, np, env, s, tg);
-            const int64_t fo = (int64_t)k * A.flag_stride + env;
-            A.reward[fo] = r;
-            A.term[fo] = term ? 1 : 0;
-            A.trunc[fo] = trunc ? 1 : 0;
+        write_obs<T, M>(A.obs + (int64_t)k * A.obs_stride, np, env, s, tg);
+        const int64_t fo = (int64_t)k * A.flag_stride + env;
+        A.reward[fo] = r;
+        A.term[fo] = term ? 1 : 0;
+        A.trunc[fo] = trunc ? 1 : 0;
+        if constexpr (kMulti) {
+#pragma unroll
+            for (int i = 0; i < M; ++i) a[i] = clip1(nxt[i]);
         }
     }
     if (valid) {
@@ -338,12 +336,14 @@ __global__ void __launch_bounds__(256) k_station_step(StationLaunch<T> L) {
         A.ep[env] = ep;
         A.et[env] = et;
     }
-    if (live) A.restart[env] = restarted ? 1 : 0;
+    A.restart[env] = restarted ? 1 : 0;
 }
 
 template <typename T, int M, bool kMulti>
 static void launch_station_body(const StationLaunch<T>& L, bool shaped, bool fins, bool payload, hipStream_t s) {
-    const dim3 grid((unsigned)((L.a.npad + 255) / 256)), block(256);
+    // npad is a multiple of 64: the largest block of up to four waves that divides it
+    const unsigned b = L.a.npad % 256 == 0 ? 256u : L.a.npad % 128 == 0 ? 128u : 64u;
+    const dim3 grid((unsigned)L.a.npad / b), block(b);
     if (payload && fins)
         hipLaunchKernelGGL((k_station_step<T, M, true, true, true, kMulti>), grid, block, 0, s, L);
     else if (payload)

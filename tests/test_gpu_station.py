@@ -363,3 +363,50 @@ def test_errors():
     st.close()
     b.close()
     t.cuda.synchronize()
+
+
+@pytest.mark.parametrize("precision", [mgx.FP32, mgx.FP64])
+@pytest.mark.parametrize("n", [1, 64, 65, 129, 256, 320])
+def test_one_call_equals_single_steps(n, precision):
+    """Block sizes of 64, 128 and 256 (the largest that divides the padded segment): a call of
+    T rows gives the outputs of T calls of one row, bit for bit, restarts included."""
+    t = torch()
+    T = 45
+    w = synth.mixed([synth.draw_class(6, 0)], [n])
+    rng = np.random.default_rng(5)
+    acts = [rng.uniform(-1.2, 1.2, size=(T, 6, n)).astype(np.float32)]
+    got = []
+    for rows in (T, 1):
+        b = make_batch(w, precision)
+        st = mgx.Station(b, **DESC)
+        st.reset(7)
+        a = t.tensor(b.pack_actions(acts), dtype=b.dtype, device=b.device)
+        outs = [{k: v.clone() for k, v in st.step(a[i:i + rows].contiguous()).items()} for i in range(0, T, rows)]
+        got.append({k: t.cat([o[k] for o in outs]).cpu().numpy() for k in outs[0]})
+        got[-1]["state"], got[-1]["episodes"] = b.get_state().cpu().numpy(), np.stack(st.episodes())
+        b.close()
+    assert got[0]["truncated"].any()
+    for k in got[0]:
+        np.testing.assert_array_equal(got[0][k], got[1][k], err_msg=k)
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+def test_nonfinite_component_ends_the_episode(bad):
+    """Environment j starts with a non-finite value in state component j: it terminates with
+    reward 0, and no other environment does."""
+    t = torch()
+    m, n = 6, 70
+    w = synth.mixed([synth.draw_class(m, 0)], [n])
+    b = make_batch(w)
+    st = mgx.Station(b)
+    st.reset(3)
+    x = b.unpack_state(b.get_state().cpu().numpy())[0].copy()
+    for j in range(13 + m):
+        x[j, j] = bad
+    b.set_state(t.tensor(b.pack_state([x]), dtype=b.dtype, device=b.device))
+    out = {k: v.cpu().numpy()[0] for k, v in st.step(b.empty_actions(1)).items()}
+    want = np.arange(out["terminated"].size) < 13 + m
+    np.testing.assert_array_equal(out["terminated"].astype(bool), want)
+    assert (out["reward"][want] == 0).all() and (out["reward"][13 + m:n] != 0).all()
+    assert np.isfinite(out["obs"]).all()
+    b.close()
