@@ -133,7 +133,8 @@ __host__ __device__ __forceinline__ void vjp_forward(const ClassT<T>& C, const E
     tp.nq[3] = fma_(qw, d3, fma_(qz, c, fma_(qx, d2, -(qy * d1))));
     const T n2 = fma_(tp.nq[3], tp.nq[3], fma_(tp.nq[2], tp.nq[2], fma_(tp.nq[1], tp.nq[1], tp.nq[0] * tp.nq[0])));
     if constexpr (std::is_same<T, double>::value) {
-        tp.g = 1.0 / sqrt_(n2);
+        T unit[4];
+        normalise64(tp.nq, n2, unit, tp.g);
     } else {
         tp.g = fma_(T(-0.5f), n2, T(1.5f));
     }

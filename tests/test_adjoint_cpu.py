@@ -122,3 +122,34 @@ def test_step_body_on_host_is_the_documented_map(variants):
     x[:13 + c.m] = state
     ref = oracle.step(env, x, a)
     assert np.allclose(s1, ref[:13 + c.m], rtol=1e-12, atol=1e-14)
+
+
+@pytest.mark.parametrize("rate", [0.0, 1e-12, 1e-3, 10.0, 49.9, 50.1, 400.0])
+@pytest.mark.parametrize("norm2", [1.0, 1.0 + 0.9e-5, 1.0 - 1.1e-5, 4.0])
+def test_double_attitude_series_and_their_fallbacks(rate, norm2):
+    """The double step's attitude increment and normalisation on both sides of the series'
+    limits (50 rad/s at this step, |q|^2 within 1e-5 of 1) against the closed forms: a body
+    without forces turns by exp(dt w / 2) and comes out normalised, to 4 units of the last
+    place; the adjoint of the attitude against central differences of the closed form."""
+    dt, m = 0.01, 1
+    w = rate * np.array([0.6, -0.64, 0.48])
+    q = np.sqrt(norm2) * np.array([0.5, 0.1, -0.7, 0.5]) / np.linalg.norm([0.5, 0.1, -0.7, 0.5])
+    # one idle thruster; no forces reach the body (dt M^-1 = 0)
+    cls = np.concatenate([np.zeros(48), np.ones(8), np.zeros(8), np.ones(3), np.zeros(3), [9.81, dt], np.ones(8)])
+    rec = np.zeros(30)
+    x = np.concatenate([np.zeros(3), q, np.zeros(3), w, np.zeros(m)])
+
+    def turned(w):
+        half = 0.5 * dt * np.linalg.norm(w)
+        d = np.concatenate([[np.cos(half)], 0.5 * dt * np.sinc(half / np.pi) * w])
+        p = np.array([q[0] * d[0] - q[1:] @ d[1:], *(q[0] * d[1:] + d[0] * q[1:] + np.cross(q[1:], d[1:]))])
+        return p / np.linalg.norm(p)
+
+    xbar = np.zeros(13 + m)
+    xbar[3:7] = [0.3, -0.2, 0.9, 0.4]
+    s, xb, _, _ = mgx.mgx_host_step_vjp(m, 0, cls, rec, x, np.zeros(m), xbar)
+    np.testing.assert_allclose(s[3:7], turned(w), rtol=0, atol=4 * 2.0 ** -53)
+    h = 1e-6 * max(1.0, rate)
+    fd = [(turned(w + h * e) - turned(w - h * e)) @ xbar[3:7] / (2 * h) for e in np.eye(3)]
+    # rounding 2^-53 / h, and the third derivative (dt / 2)^3 h^2
+    np.testing.assert_allclose(xb[10:13], fd, rtol=0, atol=8 * 2.0 ** -53 / h + (0.5 * dt) ** 3 * h * h)
