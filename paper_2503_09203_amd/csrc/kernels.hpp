@@ -312,7 +312,7 @@ template <typename T>
 hipError_t launch_gen_actions(T* out_seg, int m, int32_t npad, int64_t n_valid, int64_t env_off, int64_t rows,
                               int64_t row_stride, int64_t row_offset, uint64_t seed, hipStream_t s);
 template <typename T>
-hipError_t launch_step(const StepLaunch<T>& L, int m, int block, hipStream_t s);
+hipError_t launch_step(const StepLaunch<T>& L, int m, int block, int n_cu, hipStream_t s);
 template <typename T>
 hipError_t launch_persistent(const PersistArgs& P, int grid, int block, hipStream_t s);
 template <typename T>

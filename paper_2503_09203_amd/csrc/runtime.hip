@@ -664,10 +664,10 @@ mgx_status enqueue_step(mgx_batch* b, const void* actions, int64_t n_rows, int64
         hipError_t e;
         if (b->prec == MGX_FP32) {
             StepLaunch<float> L{a, b->h_class_f[c]};
-            e = launch_step<float>(L, b->m[c], block, b->stream);
+            e = launch_step<float>(L, b->m[c], block, b->n_cu, b->stream);
         } else {
             StepLaunch<double> L{a, b->h_class_d[c]};
-            e = launch_step<double>(L, b->m[c], block, b->stream);
+            e = launch_step<double>(L, b->m[c], block, b->n_cu, b->stream);
         }
         if (e != hipSuccess) return hip_fail(b, e, "step launch");
     }

@@ -282,7 +282,7 @@ __global__ void __launch_bounds__(256) k_station_step(StationLaunch<T> L) {
             step_body<T, M, false, kShaped, kFins, kPayload, kComp>(C, E, IA2, Brb, s, a, nullptr, &lo);
         } while (++j < A.P.substeps);
         float st[kStats];  // launch statistics are not kept by the task
-        renorm_attitude<T, M>(s, st);
+        renorm_attitude<T>(s, st);
 
         // reward and termination on the state the transition ends in
         const bool fin = finite_state<T, M>(s);

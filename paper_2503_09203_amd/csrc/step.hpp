@@ -106,11 +106,16 @@ __host__ __device__ __forceinline__ void set_amc(EnvT<T>& E, uint32_t flags) {
     for (int j = 0; j < 3; ++j) E.Ah[j] = (flags & kFlagNoAmc) ? T(0) : E.A[j];
 }
 
-template <typename T, int M>
-struct StateT {
+// Pose and velocity, and with them the rotor states.
+template <typename T>
+struct RigidT {
     T p[3];
     T q[4];
     T nu[6];
+};
+
+template <typename T, int M>
+struct StateT : RigidT<T> {
     T n[M];
 };
 
@@ -457,24 +462,19 @@ __host__ __device__ __forceinline__ void payload_solve(const EnvT<T>& E, const T
     }
 }
 
-// One step. `a` holds commands already clipped to [-1, 1]. IA2 = I + A_2 and Brb = B r_b
-// are per-environment constants hoisted out of the step loop by the caller. `forces`
-// (optional, 12 values) receives the actuator wrench and the hydrodynamic wrench of
-// Eq. (3) with d(nu)/dt the solved acceleration.
-template <typename T, int M, bool kForces = false, bool kShaped = false, bool kFins = false, bool kPayload = false,
-          bool kComp = false, bool kTape = false>
-__host__ __device__ __forceinline__ void step_body(const ClassT<T>& C, const EnvT<T>& E, const T IA2[3],
-                                                   const T Brb[3], StateT<T, M>& s, const T a[M],
-                                                   T* forces = nullptr, StateLo<T>* lo = nullptr,
-                                                   VjpTape<T>* tape = nullptr) {
-    static_assert(!(kTape && (kFins || kPayload || kComp)), "the tape covers the diagonal propeller body");
+// First part of a step: the lagged rotor states nl from the states n and the commands a
+// (already clipped to [-1, 1]), and the propellers' wrench tau. It needs nothing of the pose
+// or velocity, so a rollout's thrust can be formed ahead of its rigid-body steps.
+template <typename T, int M, bool kShaped, bool kFins = false, bool kTape = false>
+__host__ __device__ __forceinline__ void thrust_part(const ClassT<T>& C, const T n[M], const T a[M], T nl[M],
+                                                     T tau[6], VjpTape<T>* tape = nullptr) {
     // 1. rotor lag (first-order hold; alpha = 1 is the zero-order rotor)
-    T nl[M];
 #pragma unroll
-    for (int i = 0; i < M; ++i) nl[i] = fma_(C.alpha[i], a[i] - s.n[i], s.n[i]);
+    for (int i = 0; i < M; ++i) nl[i] = fma_(C.alpha[i], a[i] - n[i], n[i]);
 
     // 2. thrust and thruster layout
-    T tau[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
+#pragma unroll
+    for (int j = 0; j < 6; ++j) tau[j] = T(0);
 #pragma unroll
     for (int i = 0; i < M; ++i) {
         if constexpr (kFins) {
@@ -494,7 +494,20 @@ __host__ __device__ __forceinline__ void step_body(const ClassT<T>& C, const Env
 #pragma unroll
         for (int j = 0; j < 6; ++j) tau[j] = fma_(C.Bk[j][i], f, tau[j]);
     }
+}
 
+// Second part: pose and velocity advanced under the propellers' wrench tau (to which the
+// fins' is added, from the lagged states nl; nl is not read without fins). IA2 = I + A_2 and
+// Brb = B r_b are per-environment constants hoisted out of the step loop by the caller.
+// `forces` (optional, 12 values) receives the actuator wrench and the hydrodynamic wrench of
+// Eq. (3) with d(nu)/dt the solved acceleration.
+template <typename T, int M, bool kForces = false, bool kFins = false, bool kPayload = false, bool kComp = false,
+          bool kTape = false>
+__host__ __device__ __forceinline__ void rigid_part(const ClassT<T>& C, const EnvT<T>& E, const T IA2[3],
+                                                    const T Brb[3], RigidT<T>& s, const T* nl, T tau[6],
+                                                    T* forces = nullptr, StateLo<T>* lo = nullptr,
+                                                    VjpTape<T>* tape = nullptr) {
+    static_assert(!(kTape && (kFins || kPayload || kComp)), "the tape covers the diagonal propeller body");
     // 3. kinematics
     const T qw = s.q[0], qx = s.q[1], qy = s.q[2], qz = s.q[3];
     const T x2 = qx + qx, y2 = qy + qy, z2 = qz + qz;
@@ -672,8 +685,6 @@ __host__ __device__ __forceinline__ void step_body(const ClassT<T>& C, const Env
         const T gm1 = T(-0.5) * fma_(T(2), cr, n2m1);
 #pragma unroll
         for (int j = 0; j < 4; ++j) two_sum_acc(s.q[j], lo->q[j], s.q[j] * gm1);
-#pragma unroll
-        for (int i = 0; i < M; ++i) s.n[i] = nl[i];
         return;
     }
     T c, sh;
@@ -708,8 +719,21 @@ __host__ __device__ __forceinline__ void step_body(const ClassT<T>& C, const Env
         tape->nq[3] = nq3;
         tape->g = g;
     }
+}
+
+// One step: both parts.
+template <typename T, int M, bool kForces = false, bool kShaped = false, bool kFins = false, bool kPayload = false,
+          bool kComp = false, bool kTape = false>
+__host__ __device__ __forceinline__ void step_body(const ClassT<T>& C, const EnvT<T>& E, const T IA2[3],
+                                                   const T Brb[3], StateT<T, M>& s, const T a[M],
+                                                   T* forces = nullptr, StateLo<T>* lo = nullptr,
+                                                   VjpTape<T>* tape = nullptr) {
+    T nl[M], tau[6];
+    thrust_part<T, M, kShaped, kFins, kTape>(C, s.n, a, nl, tau, tape);
+    rigid_part<T, M, kForces, kFins, kPayload, kComp, kTape>(C, E, IA2, Brb, s, nl, tau, forces, lo, tape);
 #pragma unroll
     for (int i = 0; i < M; ++i) s.n[i] = nl[i];
 }
+
 
 }  // namespace mgx

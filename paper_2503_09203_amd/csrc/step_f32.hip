@@ -4,7 +4,7 @@
 #include "step_kernel.hpp"
 
 namespace mgx {
-template hipError_t launch_step<float>(const StepLaunch<float>&, int, int, hipStream_t);
+template hipError_t launch_step<float>(const StepLaunch<float>&, int, int, int, hipStream_t);
 }  // namespace mgx
 
 // Per-wave phase times of the last step launch (diagnostic builds; see g_wave_ts).

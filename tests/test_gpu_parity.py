@@ -482,3 +482,45 @@ def test_graph_replays_equal_eager_steps(n_steps, K):
         g2.replay()          # needs rows beyond the buffer at the current step
     bg.close()
     be.close()
+
+
+@pytest.mark.parametrize("make", ["plain", "shaped", "payload"])
+@pytest.mark.parametrize("precision", [mgx.FP32, mgx.FP64])
+@pytest.mark.parametrize("n,K", [(1, 4), (64, 5), (65, 33), (200, 36), (33000, 34), (33090, 7)])
+def test_two_wave_launches_equal_the_one_wave_form(n, K, precision, make):
+    """Launches of several steps with two waves per tile (one or four tiles per block, the last
+    block partly empty; hand-over groups cut by the last step; rows switching inside them)
+    against the same steps as three-step launches, which keep the one-wave form: states,
+    trajectories and wrenches bit for bit, statistics to their summation order."""
+    import torch as t
+    base = synth.plain_class()
+    cls = {"plain": base, "shaped": synth.propeller_variants(base), "payload": synth.payload_class()}[make]
+    w = synth.mixed([cls], [n], steps=K, hold=3)
+    b = make_batch(w, precision)
+    s0 = b.get_state()
+    acts = b.gen_actions((K + 2) // 3 + 1, seed=4)
+    L = b.layout
+    traj = t.zeros((2, K, L.state_elems), dtype=b.dtype, device=b.device)
+    forces = t.zeros((2, K, L.force_row_elems), dtype=b.dtype, device=b.device)
+    b.step(acts, K, hold=3, flags=mgx.STEP_STATS)
+    two, stats = b.get_state(), b.stats()
+    assert b.check() == (0, 0)
+    b.set_state(s0)
+    b.t = 0
+    b.step(acts, K, hold=3, traj=traj[0], forces=forces[0])
+    assert t.equal(b.get_state(), two)
+    b.set_state(s0)
+    b.t = 0
+    for k in range(0, K, 3):
+        b.step(acts, min(3, K - k), hold=3, traj=traj[1][k:], forces=forces[1][k:], flags=mgx.STEP_STATS)
+    assert t.equal(traj[0], traj[1]) and t.equal(forces[0], forces[1])
+    one = b.get_state()
+    if precision == mgx.FP64:
+        assert t.equal(one, two)
+    else:       # a launch's end renormalises attitudes that drifted by more than 1e-6
+        t.testing.assert_close(one, two, rtol=0, atol=2e-6)
+    ref = b.stats()
+    for f in ("max_speed", "mean_speed", "max_rate", "mean_rate", "mean_kinetic"):
+        np.testing.assert_allclose(getattr(stats, f)[0], getattr(ref, f)[0], rtol=1e-4)
+    assert stats.n_nonfinite[0] == ref.n_nonfinite[0] == 0
+    b.close()
