@@ -25,26 +25,37 @@ constexpr int kAheadTiles = 4;  // tiles per block at most
 // (1000 steps of 8,192 environments: 346 us in groups of two, 335 us), of two in a short one,
 // where the rigid-body wave waits for the first group (16-step launches of 65,536: 10.3 us,
 // 10.7 in groups of four, 10.75 in the one-wave form), and of two in double (no difference).
-// The ring holds two groups per tile, 12 KB.
-template <typename T>
+// A step's hand-over is the propellers' wrench and, with fins, the sines and cosines of the M
+// deflections. The ring holds two groups per tile: 12 KB, or up to 22 KB with fins in groups
+// of two (four tiles in groups of four would not fit a compute unit's LDS).
+template <typename T, int M, bool kFins>
 struct AheadRing {
-    static constexpr int kGroup = sizeof(T) == 4 ? 4 : 2;
-    T tau[2][kGroup][6][kWave];
+    static constexpr int kGroup = sizeof(T) == 4 && !kFins ? 4 : 2;
+    static constexpr int kRows = 6 + (kFins ? 2 * M : 0);
+    T x[2][kGroup][kRows][kWave];
     static __device__ __forceinline__ int group(int K) { return K > 32 ? kGroup : 2; }
 };
 
+// End of the hand-over group that starts at step k0: `group` steps on, or the end of the
+// stretch of `seg` steps (which both waves keep in `end`) or of the launch.
+__device__ __forceinline__ int ahead_group_end(int k0, int group, int seg, int K, int& end) {
+    if (k0 == end) end += seg;
+    if (end > K) end = K;
+    return k0 + group < end ? k0 + group : end;
+}
+
 // The thrust wave: rotor states, command rows and their bookkeeping as in env_steps.
-template <typename T, int M, bool kOut, bool kShaped>
+template <typename T, int M, bool kOut, bool kShaped, bool kFins, bool kSeg>
 __device__ __forceinline__ void ahead_thrust(const StepArgs& A, const ClassT<T>& Cs, int64_t env, int lane, bool live,
-                                             int64_t t0, AheadRing<T>& ring, bool* fin_out) {
-    const int group = AheadRing<T>::group(A.K);
+                                             int64_t t0, AheadRing<T, M, kFins>& ring) {
+    const int group = ring.group(A.K);
     const int64_t np = A.npad;
     T* S = (T*)A.state + kStateFixed * np + env;
     T n[M], cur[M], nxt[M];
 #pragma unroll
     for (int i = 0; i < M; ++i) n[i] = S[i * np];
-    const ClassT<T> C = class_in_vgpr<T, M>(Cs);
-    const int K = A.K;
+    const ClassT<T> C = class_in_vgpr<T, M, false, kFins>(Cs);
+    const int K = A.K, seg = A.seg;
     const int64_t hold = A.hold, nrows = A.n_rows, rstride = A.row_stride;
     const T* abase = (const T*)A.actions + env;
     auto clamp_row = [nrows](int64_t x) { return x < 0 ? (int64_t)0 : (x >= nrows ? nrows - 1 : x); };
@@ -62,13 +73,15 @@ __device__ __forceinline__ void ahead_thrust(const StepArgs& A, const ClassT<T>&
     __builtin_amdgcn_s_waitcnt(0);
 #pragma unroll
     for (int i = 0; i < M; ++i) cur[i] = clip1(cur[i]);
-    for (int k0 = 0, buf = 0; k0 < K; k0 += group, buf ^= 1) {
-        const int k1 = k0 + group < K ? k0 + group : K;
+    [[clang::code_align(64)]] for (int k0 = 0, buf = 0, end = seg; k0 < K; buf ^= 1) {
+        const int k1 = kSeg ? ahead_group_end(k0, group, seg, K, end) : k0 + group < K ? k0 + group : K;
         [[clang::code_align(64)]] for (int k = k0; k < k1; ++k) {
-            T nl[M], tau[6];
-            thrust_part<T, M, kShaped>(C, n, cur, nl, tau);
+            constexpr int kRows = AheadRing<T, M, kFins>::kRows;
+            T nl[M], x[kRows];
+            thrust_part<T, M, kShaped, kFins>(C, n, cur, nl, x);
+            if constexpr (kFins) fin_angles<T, M>(C, nl, x + 6);
 #pragma unroll
-            for (int j = 0; j < 6; ++j) ring.tau[buf][k - k0][j][lane] = tau[j];
+            for (int j = 0; j < kRows; ++j) ring.x[buf][k - k0][j][lane] = x[j];
 #pragma unroll
             for (int i = 0; i < M; ++i) n[i] = nl[i];
             if constexpr (kOut) {
@@ -89,13 +102,10 @@ __device__ __forceinline__ void ahead_thrust(const StepArgs& A, const ClassT<T>&
                 if (k + 1 + hold < K && r + 1 >= nrows) bad = true;
             }
         }
+        k0 = kSeg ? k1 : k0 + group;
         __syncthreads();
     }
     if (bad && lane == 0) atomicOr(&A.misc->err, kErrActionRow);
-    bool fin = true;
-#pragma unroll
-    for (int i = 0; i < M; ++i) fin &= finite_(n[i]);
-    *fin_out = fin;
     if (live) {
 #pragma unroll
         for (int i = 0; i < M; ++i) S[i * np] = n[i];
@@ -103,30 +113,39 @@ __device__ __forceinline__ void ahead_thrust(const StepArgs& A, const ClassT<T>&
 }
 
 // The rigid-body wave.
-template <typename T, int M, bool kOut, bool kPayload>
-__device__ __forceinline__ void ahead_rigid(const StepArgs& A, const ClassT<T>& C, int64_t env, int lane, bool live,
-                                            const AheadRing<T>& ring, EnvT<T>& E, T IA2[3], RigidT<T>& s,
-                                            float st[kStats]) {
-    const int group = AheadRing<T>::group(A.K);
+template <typename T, int M, bool kOut, bool kFins, bool kPayload, bool kSeg>
+__device__ __forceinline__ void ahead_rigid(const StepArgs& A, const ClassT<T>& Cs, int64_t env, int lane, bool live,
+                                            const AheadRing<T, M, kFins>& ring) {
+    const int group = ring.group(A.K);
     const int64_t np = A.npad;
     MGX_WAVE_TS(ts_entry);
+    RigidT<T> s;
+    EnvT<T> E;
+    T IA2[3], Brb[3];
+    float st[kStats];  // launches with statistics run the one-wave form
     load_rigid<T>((const T*)A.state, np, env, s);
-    load_record<T, kPayload>((const T*)A.rec, np, env, C.flags, E);
-    T Brb[3];
+    load_record<T, kPayload>((const T*)A.rec, np, env, Cs.flags, E);
+    const ClassT<T> C = fins_in_vgpr<T, M, kFins>(Cs);
+    // classes with fins carry the attitude's low-order words through a stretch (float)
+    constexpr bool kComp = kFins && std::is_same<T, float>::value;
+    StateLo<T> lo;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) lo.q[j] = T(0);
     env_prologue<T, kPayload>(C, E, IA2, Brb);
     __builtin_amdgcn_s_waitcnt(0);
     MGX_WAVE_TS(ts_loaded);
-    const int K = A.K;
-    for (int k0 = 0, buf = 0; k0 < K; k0 += group, buf ^= 1) {
-        const int k1 = k0 + group < K ? k0 + group : K;
+    const int K = A.K, seg = A.seg;
+    [[clang::code_align(64)]] for (int k0 = 0, buf = 0, end = seg; k0 < K; buf ^= 1) {
+        const int k1 = kSeg ? ahead_group_end(k0, group, seg, K, end) : k0 + group < K ? k0 + group : K;
         __syncthreads();
         [[clang::code_align(64)]] for (int k = k0; k < k1; ++k) {
-            T tau[6];
+            constexpr int kRows = AheadRing<T, M, kFins>::kRows;
+            T x[kRows];
 #pragma unroll
-            for (int j = 0; j < 6; ++j) tau[j] = ring.tau[buf][k - k0][j][lane];
+            for (int j = 0; j < kRows; ++j) x[j] = ring.x[buf][k - k0][j][lane];
             if constexpr (kOut) {
                 T f[kForceLen];
-                rigid_part<T, M, true, false, kPayload>(C, E, IA2, Brb, s, nullptr, tau, f);
+                rigid_part<T, M, true, kFins, kPayload, kComp, false, true>(C, E, IA2, Brb, s, x + 6, x, f, &lo);
                 if (live) {
                     if (A.forces) {
                         T* fo = (T*)A.forces + k * A.force_stride + env;
@@ -136,7 +155,15 @@ __device__ __forceinline__ void ahead_rigid(const StepArgs& A, const ClassT<T>& 
                     if (A.traj) store_rigid<T>((T*)A.traj + k * A.traj_stride, np, env, s);
                 }
             } else {
-                rigid_part<T, M, false, false, kPayload>(C, E, IA2, Brb, s, nullptr, tau);
+                rigid_part<T, M, false, kFins, kPayload, kComp, false, true>(C, E, IA2, Brb, s, x + 6, x, nullptr, &lo);
+            }
+        }
+        k0 = kSeg ? k1 : k0 + group;
+        if constexpr (kSeg) {
+            if (k1 == end && k1 < K) {
+                renorm_attitude<T>(s, st);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) lo.q[j] = T(0);
             }
         }
     }
@@ -158,12 +185,11 @@ __device__ __forceinline__ void ahead_rigid(const StepArgs& A, const ClassT<T>& 
 // Blocks of up to kAheadTiles tiles: the first half of a block's waves are the rigid-body
 // waves, so that with four tiles each SIMD of the compute unit holds one wave of either
 // kind. Waves past the segment run its last tile and store nothing.
-template <typename T, int M, bool kOut, bool kShaped, bool kPayload>
+// kSeg: the launch holds several stretches of A.seg steps (a kernel of its own: the cut of
+// the hand-over groups at the stretches' ends costs a double launch of one stretch 10%).
+template <typename T, int M, bool kOut, bool kShaped, bool kFins, bool kPayload, bool kSeg>
 __global__ void __launch_bounds__(2 * kAheadTiles * kWave) k_step_ahead(StepLaunch<T> L) {
-    __shared__ AheadRing<T> rings[kAheadTiles];
-    __shared__ float red[2 * kAheadTiles][kStats];
-    __shared__ uint8_t rotors_finite[kAheadTiles][kWave];
-    __shared__ int is_last;
+    __shared__ AheadRing<T, M, kFins> rings[kAheadTiles];
     const StepArgs& A = L.a;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int tiles = blockDim.x / (2 * kWave), wv = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -171,41 +197,15 @@ __global__ void __launch_bounds__(2 * kAheadTiles * kWave) k_step_ahead(StepLaun
     const int64_t tile = (int64_t)blockIdx.x * tiles + slot, last = A.npad / kWave - 1;
     const bool live = tile <= last;
     const int64_t env = (live ? tile : last) * kWave + lane;
-    float st[kStats];
-#pragma unroll
-    for (int j = 0; j < kStats; ++j) st[j] = 0.0f;
     const int64_t t0 = A.misc->t[A.rd];
     if (blockIdx.x == 0 && tid == 0) {
         if (A.advance) A.misc->t[A.wr] = t0 + A.advance;
         prepare_next_slot(A.misc, A.wr);
     }
-    if (wv >= tiles) {
-        bool fin;
-        ahead_thrust<T, M, kOut, kShaped>(A, L.cls, env, lane, live, t0, rings[slot], &fin);
-        if (!A.partials) return;
-        rotors_finite[slot][lane] = fin ? 1 : 0;
-        __syncthreads();
-    } else {
-        EnvT<T> E;
-        RigidT<T> s;
-        T IA2[3];
-        ahead_rigid<T, M, kOut, kPayload>(A, L.cls, env, lane, live, rings[slot], E, IA2, s, st);
-        if (!A.partials) return;
-        __syncthreads();
-        T m = T(0);
-#pragma unroll
-        for (int j = 0; j < 3; ++j) m = __builtin_elementwise_maximum(m, abs_(s.p[j]));
-#pragma unroll
-        for (int j = 0; j < 4; ++j) m = __builtin_elementwise_maximum(m, abs_(s.q[j]));
-#pragma unroll
-        for (int j = 0; j < 6; ++j) m = __builtin_elementwise_maximum(m, abs_(s.nu[j]));
-        env_stats<T, kPayload>(E, IA2, s, m <= (T)3.0e38 && rotors_finite[slot][lane], live && env < A.nvalid, st);
-        if (!live) {
-#pragma unroll
-            for (int j = 0; j < kStats; ++j) st[j] = 0.0f;
-        }
-    }
-    finish_stats(A, st, red, &is_last);
+    if (wv >= tiles)
+        ahead_thrust<T, M, kOut, kShaped, kFins, kSeg>(A, L.cls, env, lane, live, t0, rings[slot]);
+    else
+        ahead_rigid<T, M, kOut, kFins, kPayload, kSeg>(A, L.cls, env, lane, live, rings[slot]);
 }
 
 }  // namespace mgx

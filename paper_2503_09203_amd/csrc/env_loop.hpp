@@ -262,26 +262,6 @@ __device__ __forceinline__ void final_reduce_stats(const float* partials, unsign
     out[j] = acc;
 }
 
-// Launch statistics: block partials, then the last block to finish reduces them in order.
-// Every thread of the block calls it.
-__device__ __forceinline__ void finish_stats(const StepArgs& A, const float st[kStats], float (*red)[kStats],
-                                             int* is_last) {
-    const int tid = threadIdx.x;
-    block_reduce_stats(st, red, A.partials + (int64_t)blockIdx.x * kStats);
-    __threadfence();
-    __syncthreads();
-    if (tid == 0) {
-        const unsigned prev = atomicAdd(&A.misc->done[A.class_index], 1u);
-        *is_last = (prev == gridDim.x - 1);
-    }
-    __syncthreads();
-    if (*is_last) {
-        __threadfence();
-        if (tid < kStats) final_reduce_stats(A.partials, gridDim.x, tid, A.stats);
-        if (tid == 0) atomicExch(&A.misc->done[A.class_index], 0u);
-    }
-}
-
 #ifdef MGX_WAVE_TIMESTAMPS
 // Diagnostic builds only: per-wave phase times of the step loop on the 100 MHz real-time
 // counter (entry; prologue loads landed; steps done; stores drained), indexed by the wave's
@@ -321,8 +301,8 @@ __device__ __forceinline__ int64_t uniform64(int64_t x) {
 // fins, the per-actuator arrays (k-scaled layout columns, lag factors, fin geometry and
 // gains) move to vector registers; up to six propellers they fit the scalar file next to
 // the loop's own scalars and stay there.
-template <typename T, int M, bool kFins = false, bool kAlways = false>
-__device__ __forceinline__ ClassT<T> class_in_vgpr(const ClassT<T>& Cs) {
+template <typename T, int M, bool kFins>
+__device__ __forceinline__ ClassT<T> fins_in_vgpr(const ClassT<T>& Cs) {
     ClassT<T> C = Cs;
     if constexpr (kFins) {
 #pragma unroll
@@ -339,6 +319,12 @@ __device__ __forceinline__ ClassT<T> class_in_vgpr(const ClassT<T>& Cs) {
             C.fin_kd[i] = in_vgpr(Cs.fin_kd[i]);
         }
     }
+    return C;
+}
+
+template <typename T, int M, bool kFins = false, bool kAlways = false>
+__device__ __forceinline__ ClassT<T> class_in_vgpr(const ClassT<T>& Cs) {
+    ClassT<T> C = fins_in_vgpr<T, M, kFins>(Cs);
     if constexpr (M > 6 || kFins || kAlways) {
 #pragma unroll
         for (int i = 0; i < M; ++i) {
@@ -449,47 +435,6 @@ __device__ __forceinline__ void renorm_attitude(RigidT<T>& s, float st[kStats]) 
     st[kStMaxDrift] = (float)drift;
 }
 
-// Statistics of one environment at the end of a launch (renormalisation and drift are in st
-// already): speeds and kinetic energy of a finite state, the non-finite count otherwise.
-template <typename T, bool kPayload>
-__device__ __forceinline__ void env_stats(const EnvT<T>& E, const T IA2[3], const RigidT<T>& s, bool fin, bool valid,
-                                          float st[kStats]) {
-    // every slot is written on every path (stores that differ by branch would keep the array
-    // in scratch memory)
-    const bool ok = valid && fin;
-    float sp = 0.0f, rt = 0.0f, kin = 0.0f;
-    if (ok) {
-        sp = (float)sqrt_(s.nu[0] * s.nu[0] + s.nu[1] * s.nu[1] + s.nu[2] * s.nu[2]);
-        rt = (float)sqrt_(s.nu[3] * s.nu[3] + s.nu[4] * s.nu[4] + s.nu[5] * s.nu[5]);
-        // nu^T (M_RB + M_A) nu. Diagonal M: (m + A_j) v_j^2 + (I_j + A_{3+j}) w_j^2.
-        // With a payload the full M: m |v|^2 + A_1 v.v - 2 v.(m r_g x w) + w^T (I_o + A_2) w.
-        const T* v = s.nu;
-        const T* w = s.nu + 3;
-        T ke = T(0);
-        if constexpr (kPayload) {
-            T mrw[3], Iw[3];
-            cross(E.mrg, w, mrw);
-            Iw[0] = fma_(E.IoA[4], w[2], fma_(E.IoA[3], w[1], E.IoA[0] * w[0]));
-            Iw[1] = fma_(E.IoA[5], w[2], fma_(E.IoA[1], w[1], E.IoA[3] * w[0]));
-            Iw[2] = fma_(E.IoA[2], w[2], fma_(E.IoA[5], w[1], E.IoA[4] * w[0]));
-#pragma unroll
-            for (int j = 0; j < 3; ++j) ke += v[j] * ((E.mass + E.A[j]) * v[j] - T(2) * mrw[j]) + w[j] * Iw[j];
-        } else {
-#pragma unroll
-            for (int j = 0; j < 3; ++j) ke += (E.mass + E.A[j]) * (v[j] * v[j]) + IA2[j] * (w[j] * w[j]);
-        }
-        kin = (float)(T(0.5) * ke);
-    }
-    st[kStMaxSpeed] = sp;
-    st[kStSumSpeed] = sp;
-    st[kStMaxRate] = rt;
-    st[kStSumRate] = rt;
-    st[kStSumKin] = kin;
-    st[kStNonFinite] = valid && !fin ? 1.0f : 0.0f;
-    st[kStMaxDrift] = ok ? st[kStMaxDrift] : 0.0f;
-    st[kStRenorm] = ok ? st[kStRenorm] : 0.0f;
-}
-
 // K steps of environment `env` (a slot of the segment described by A) from global step
 // t0. Commands are fetched raw one hold interval before use and clipped when their row
 // becomes current; all prologue loads are drained once before the loop so that the only
@@ -585,12 +530,14 @@ __device__ __forceinline__ void env_steps(const StepArgs& A, const ClassT<T>& Cs
     } else {
 
     // Runs of steps between action-row switches: the inner loop carries only its counter,
-    // and the row bookkeeping happens once per hold interval.
+    // and the row bookkeeping happens once per hold interval. Loops start on a cache line of
+    // instructions: a taken branch into the end of one costs a lone wave a second fetch (up to
+    // 7% of a step, by where the code happens to lie).
     int k = 0;
     while (k < K) {
         const int64_t left = hold - phase;  // steps until the next row switch, >= 1
         const int run = (int64_t)(K - k) < left ? K - k : (int)left;
-        for (int j = 0; j < run; ++j, ++k) {
+        [[clang::code_align(64)]] for (int j = 0; j < run; ++j, ++k) {
             if constexpr (kOut) {
                 T f[kForceLen];
                 step_body<T, M, true, kShaped, kFins, kPayload, kComp>(C, E, IA2, Brb, s, cur, f, &lo);
@@ -660,7 +607,54 @@ __device__ __forceinline__ void env_steps(const StepArgs& A, const ClassT<T>& Cs
     }
 #endif
 
-    if (A.partials) env_stats<T, kPayload>(E, IA2, s, finite_state<T, M>(s), env < A.nvalid, st);
+    if (A.partials) {
+        if (env < A.nvalid) {
+            bool fin = true;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) fin &= finite_(s.p[j]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) fin &= finite_(s.q[j]);
+#pragma unroll
+            for (int j = 0; j < 6; ++j) fin &= finite_(s.nu[j]);
+#pragma unroll
+            for (int i = 0; i < M; ++i) fin &= finite_(s.n[i]);
+            if (fin) {
+                float sp = (float)sqrt_(s.nu[0] * s.nu[0] + s.nu[1] * s.nu[1] + s.nu[2] * s.nu[2]);
+                float rt = (float)sqrt_(s.nu[3] * s.nu[3] + s.nu[4] * s.nu[4] + s.nu[5] * s.nu[5]);
+                // nu^T (M_RB + M_A) nu. Diagonal M: (m + A_j) v_j^2 + (I_j + A_{3+j}) w_j^2.
+                // With a payload the full M: m |v|^2 + A_1 v.v - 2 v.(m r_g x w) + w^T (I_o + A_2) w.
+                const T* v = s.nu;
+                const T* w = s.nu + 3;
+                T ke = T(0);
+                if constexpr (kPayload) {
+                    T mrw[3], Iw[3];
+                    cross(E.mrg, w, mrw);
+                    Iw[0] = fma_(E.IoA[4], w[2], fma_(E.IoA[3], w[1], E.IoA[0] * w[0]));
+                    Iw[1] = fma_(E.IoA[5], w[2], fma_(E.IoA[1], w[1], E.IoA[3] * w[0]));
+                    Iw[2] = fma_(E.IoA[2], w[2], fma_(E.IoA[5], w[1], E.IoA[4] * w[0]));
+#pragma unroll
+                    for (int j = 0; j < 3; ++j)
+                        ke += v[j] * ((E.mass + E.A[j]) * v[j] - T(2) * mrw[j]) + w[j] * Iw[j];
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 3; ++j)
+                        ke += (E.mass + E.A[j]) * (v[j] * v[j]) + IA2[j] * (w[j] * w[j]);
+                }
+                st[kStMaxSpeed] = sp;
+                st[kStSumSpeed] = sp;
+                st[kStMaxRate] = rt;
+                st[kStSumRate] = rt;
+                st[kStSumKin] = (float)(T(0.5) * ke);
+            } else {
+                st[kStNonFinite] = 1.0f;
+                st[kStMaxDrift] = 0.0f;
+                st[kStRenorm] = 0.0f;
+            }
+        } else {
+            st[kStRenorm] = 0.0f;
+            st[kStMaxDrift] = 0.0f;
+        }
+    }
 }
 
 }  // namespace mgx

@@ -213,9 +213,7 @@ struct PersistArgs {
     int32_t hold, K;
     DevMisc* misc;
     int32_t rd, wr, advance;
-    int32_t n_heavy;       // tiles [0, n_heavy) go first to the first wave on each SIMD
     int32_t any_shaped;    // some class has dead zones or reverse gains: the kernel with both bodies
-    uint32_t* simd_rank;   // [kSimdKeys] arrival table, or null
     float* tile_partials;  // [n_tiles][kStats] or null
     double* stats;         // [16][kStats]
 };
@@ -241,6 +239,11 @@ struct StepArgs {
     int64_t n_rows, row0;
     int32_t class_index;
     int32_t advance;      // 0, or K: block 0 writes t[wr] = t[rd] + K
+    // Steps between the checks of the attitude's drift; K (at the launch's end only) but in the
+    // two-wave form, where a captured chunk runs many stretches in one launch with the checks,
+    // and the results, of as many launches.
+    int32_t seg;
+    int32_t pad;
     void* traj;           // class segment base within step row 0, or null
     int64_t traj_stride;  // elements per step row
     void* forces;         // class segment base within step row 0, or null
@@ -248,6 +251,18 @@ struct StepArgs {
     float* partials;      // [gridDim.x][kStats] or null (no statistics)
     double* stats;        // [kStats] of this class, written by the last block
 };
+
+// The fewest steps per launch that the two-wave form takes: with fewer than one hand-over's
+// worth of steps after the first it has nothing to overlap.
+constexpr int kAheadMinSteps = 4;
+
+// Whether a class launch of K steps runs two waves per tile (ahead.hpp): while the device has
+// a SIMD for each tile (1000 steps of 65,536 environments 387 us, 437 with one wave). Beyond,
+// a SIMD's waves fill it by themselves and the hand-over only adds work. Fin classes in double
+// stay on one wave: the deflections of four tiles do not fit a compute unit's LDS.
+inline bool two_waves(int64_t npad, int32_t K, bool double_fins, int n_cu) {
+    return !double_fins && K >= kAheadMinSteps && npad / kWave <= 4 * (int64_t)n_cu;
+}
 
 template <typename T>
 struct StepLaunch {

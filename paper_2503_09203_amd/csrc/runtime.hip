@@ -594,7 +594,7 @@ static int64_t floor_div_h(int64_t a, int64_t b) {
 namespace mgx {
 // Enqueues K steps of every class; `advance` of the last class launch moves the counter.
 mgx_status enqueue_step(mgx_batch* b, const void* actions, int64_t n_rows, int64_t row0, int32_t hold, int32_t K,
-                        bool stats, void* traj, void* forces, int block, int64_t t_hint) {
+                        int32_t seg, bool stats, void* traj, void* forces, int block, int64_t t_hint) {
     const size_t P = (size_t)b->prec;
     bool fins = false;
     for (int c = 0; c < b->n_classes; ++c) fins = fins || b->h_class_f[c].fin_mask != 0 || b->h_class_f[c].payload != 0;
@@ -647,6 +647,7 @@ mgx_status enqueue_step(mgx_batch* b, const void* actions, int64_t n_rows, int64
         a.misc = b->d_misc;
         a.class_index = c;
         a.advance = (c == b->n_classes - 1) ? K : 0;
+        a.seg = seg;
         a.rd = b->slot;
         a.wr = 1 - b->slot;
         // a hint whose row lies outside the buffer is dropped: the launch then finds (and
@@ -701,14 +702,14 @@ extern "C" mgx_status mgx_batch_step(mgx_batch* b, const void* actions, int64_t 
     if (flags & MGX_STEP_UNFUSED) {
         const size_t P = (size_t)b->prec;
         for (int32_t k = 0; k < K; ++k) {
-            mgx_status s = enqueue_step(b, actions, n_rows, row0, hold, 1, stats && k == K - 1,
+            mgx_status s = enqueue_step(b, actions, n_rows, row0, hold, 1, 1, stats && k == K - 1,
                                         traj ? (char*)traj + P * k * b->state_elems : nullptr,
                                         forces ? (char*)forces + P * k * b->force_row_elems : nullptr, b->block,
                                         b->host_t + k);
             if (s != MGX_OK) return s;
         }
     } else {
-        mgx_status s = enqueue_step(b, actions, n_rows, row0, hold, K, stats, traj, forces, b->block, b->host_t);
+        mgx_status s = enqueue_step(b, actions, n_rows, row0, hold, K, K, stats, traj, forces, b->block, b->host_t);
         if (s != MGX_OK) return s;
     }
     b->host_t += K;

@@ -146,8 +146,9 @@ ClassDesc64 to_desc64(const mgx_class_desc& c);
 // Enqueues K steps of every class and flips the counter slot. t_hint: the step count the
 // launches are expected to start at when they run (-1 if unknown); any value is correct,
 // a matching one saves the single-step launch a dependent memory round trip.
+// seg: steps between the checks of the attitude's drift, <= K (K: one check at the end).
 mgx_status enqueue_step(mgx_batch* b, const void* actions, int64_t n_rows, int64_t row0, int32_t hold, int32_t K,
-                        bool stats, void* traj, void* forces, int block, int64_t t_hint);
+                        int32_t seg, bool stats, void* traj, void* forces, int block, int64_t t_hint);
 mgx_status validate_rows(const mgx_batch* b, int64_t t0, int64_t n_rows, int64_t row0, int32_t hold, int64_t K);
 // Redraws the parameters of the environments whose byte in `mask` is set, with epochs[e] as
 // the draw's epoch (both device arrays of n_pad_total, environment e of class c at

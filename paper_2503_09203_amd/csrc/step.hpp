@@ -228,9 +228,11 @@ __host__ __device__ __forceinline__ void sincos_deflection(T x, T& s, T& c) {
 // sin(d) u_n, so no angle is formed. Lift K_L sin(a)cos(a)|u_p|^2 acts along
 // span x u_p / |u_p| = (u_c n - u_n c) / |u_p|, drag (K_D0 + K_D sin^2(a))|u_p|^2 along
 // -u_p / |u_p|; the force F acts at r_i, adding [F; r_i x F].
-template <typename T, int M>
-__host__ __device__ __forceinline__ void add_fin_wrench(const ClassT<T>& C, const T nl[M], const T vr[3],
-                                                        const T w[3], T tau[6]) {
+// x holds the lagged states, or (kAngles) the sines of the deflections and then their cosines,
+// formed ahead by fin_angles.
+template <typename T, int M, bool kAngles = false>
+__host__ __device__ __forceinline__ void add_fin_wrench(const ClassT<T>& C, const T* x, const T vr[3], const T w[3],
+                                                        T tau[6]) {
 #pragma unroll
     for (int i = 0; i < M; ++i) {
         if (!((C.fin_mask >> i) & 1u)) continue;
@@ -241,7 +243,12 @@ __host__ __device__ __forceinline__ void add_fin_wrench(const ClassT<T>& C, cons
         const T un = fma_(u[2], C.fin_n[i][2], fma_(u[1], C.fin_n[i][1], u[0] * C.fin_n[i][0]));
         const T wp2 = fma_(un, un, uc * uc);
         T sd, cd;
-        sincos_deflection(C.fin_max[i] * nl[i], sd, cd);
+        if constexpr (kAngles) {
+            sd = x[i];
+            cd = x[M + i];
+        } else {
+            sincos_deflection(C.fin_max[i] * x[i], sd, cd);
+        }
         const T sa = fma_(sd, uc, -(cd * un));  // |u_p| sin(a)
         const T ca = fma_(cd, uc, sd * un);     // |u_p| cos(a)
         const T inv = wp2 > T(0) ? rsqrt_(wp2) : T(0);
@@ -316,6 +323,17 @@ __host__ __device__ __forceinline__ void normalise64(const double nq[4], double 
         const double ge = 1.0 / sqrt_(n2);
         g = far ? ge : g;
         for (int j = 0; j < 4; ++j) out[j] = far ? nq[j] * ge : out[j];
+    }
+}
+
+// Sines (x[0 .. M - 1]) and cosines (x[M .. 2 M - 1]) of the fins' deflections from the lagged
+// states; 0 for propellers.
+template <typename T, int M>
+__host__ __device__ __forceinline__ void fin_angles(const ClassT<T>& C, const T nl[M], T x[2 * M]) {
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+        x[i] = x[M + i] = T(0);
+        if ((C.fin_mask >> i) & 1u) sincos_deflection(C.fin_max[i] * nl[i], x[i], x[M + i]);
     }
 }
 
@@ -497,14 +515,15 @@ __host__ __device__ __forceinline__ void thrust_part(const ClassT<T>& C, const T
 }
 
 // Second part: pose and velocity advanced under the propellers' wrench tau (to which the
-// fins' is added, from the lagged states nl; nl is not read without fins). IA2 = I + A_2 and
+// fins' is added, from the lagged states or, with kAngles, from the deflections' sines and
+// cosines in fin; not read without fins). IA2 = I + A_2 and
 // Brb = B r_b are per-environment constants hoisted out of the step loop by the caller.
 // `forces` (optional, 12 values) receives the actuator wrench and the hydrodynamic wrench of
 // Eq. (3) with d(nu)/dt the solved acceleration.
 template <typename T, int M, bool kForces = false, bool kFins = false, bool kPayload = false, bool kComp = false,
-          bool kTape = false>
+          bool kTape = false, bool kAngles = false>
 __host__ __device__ __forceinline__ void rigid_part(const ClassT<T>& C, const EnvT<T>& E, const T IA2[3],
-                                                    const T Brb[3], RigidT<T>& s, const T* nl, T tau[6],
+                                                    const T Brb[3], RigidT<T>& s, const T* fin, T tau[6],
                                                     T* forces = nullptr, StateLo<T>* lo = nullptr,
                                                     VjpTape<T>* tape = nullptr) {
     static_assert(!(kTape && (kFins || kPayload || kComp)), "the tape covers the diagonal propeller body");
@@ -541,7 +560,7 @@ __host__ __device__ __forceinline__ void rigid_part(const ClassT<T>& C, const En
     }
     const T* v = s.nu;
     const T* w = s.nu + 3;
-    if constexpr (kFins) add_fin_wrench<T, M>(C, nl, vr, w, tau);
+    if constexpr (kFins) add_fin_wrench<T, M, kAngles>(C, fin, vr, w, tau);
 
     // 4. forces, accumulated per degree of freedom into the right-hand side F of
     // M dnu/dt = F (every term evaluated at the step-start velocity)

@@ -11,10 +11,6 @@ namespace mgx {
 
 // ----------------------------------------------------------------------------- step
 
-// The fewest steps per launch that the two-wave form takes: with fewer than one hand-over's
-// worth of steps after the first it has nothing to overlap.
-constexpr int kAheadMinSteps = 4;
-
 // K steps of every environment of one class segment; state in registers throughout.
 // kShaped: the class has dead zones or direction-dependent gains; kFins: it has fins;
 // kPayload: its centre of gravity is off the body origin (fin and payload classes take the
@@ -50,29 +46,42 @@ __global__ void __launch_bounds__(256) k_step(StepLaunch<T> L) {
         if (env < A.npad) env_steps<T, M, kOut, kShaped, kSingle, kFins, kPayload>(A, L.cls, env, t0, A.K, st);
     }
     if (!A.partials) return;
+    // Statistics: block partials, then the last block to finish reduces them in order.
     __shared__ float red[256 / kWave][kStats];
     __shared__ int is_last;
-    finish_stats(A, st, red, &is_last);
+    block_reduce_stats(st, red, A.partials + (int64_t)blockIdx.x * kStats);
+    __threadfence();
+    __syncthreads();
+    if (tid == 0) {
+        const unsigned prev = atomicAdd(&A.misc->done[A.class_index], 1u);
+        is_last = (prev == gridDim.x - 1);
+    }
+    __syncthreads();
+    if (is_last) {
+        __threadfence();
+        if (tid < kStats) final_reduce_stats(A.partials, gridDim.x, tid, A.stats);
+        if (tid == 0) atomicExch(&A.misc->done[A.class_index], 0u);
+    }
 }
 
 template <typename T, int M, bool kShaped, bool kFins, bool kPayload = false>
 static void launch_step_body(const StepLaunch<T>& L, unsigned grid, int block, bool out, bool single,
                              int n_cu, hipStream_t s) {
-    if constexpr (!kFins) {
-        // Two waves per tile while the device has a SIMD for each tile (1000 steps of 65,536
-        // environments 387 us, 437 with one wave); beyond, a SIMD's waves fill it by themselves
-        // and the hand-over only adds work. Four tiles to a block from two per compute unit
-        // on, so that every SIMD holds one wave of either kind (a block's waves go round the
-        // SIMDs); fewer are spread over more units. Fin classes stay on one wave: their wrench
-        // needs the velocity.
-        const int64_t tiles = L.a.npad / kWave;
-        if (L.a.K >= kAheadMinSteps && tiles <= 4 * (int64_t)n_cu) {
+    constexpr bool kDoubleFins = kFins && std::is_same<T, double>::value;
+    if constexpr (!kDoubleFins) {
+        if (!L.a.partials && two_waves(L.a.npad, L.a.K, kDoubleFins, n_cu)) {
+            // Four tiles to a block from two per compute unit on, so that every SIMD holds one
+            // wave of either kind (a block's waves go round the SIMDs); fewer are spread over
+            // more units.
+            const int64_t tiles = L.a.npad / kWave;
             const int per = tiles > 2 * (int64_t)n_cu ? kAheadTiles : 1;
             const dim3 g((unsigned)((tiles + per - 1) / per)), b(2 * per * kWave);
             if (out)
-                hipLaunchKernelGGL((k_step_ahead<T, M, true, kShaped, kPayload>), g, b, 0, s, L);
+                hipLaunchKernelGGL((k_step_ahead<T, M, true, kShaped, kFins, kPayload, false>), g, b, 0, s, L);
+            else if (L.a.seg < L.a.K)
+                hipLaunchKernelGGL((k_step_ahead<T, M, false, kShaped, kFins, kPayload, true>), g, b, 0, s, L);
             else
-                hipLaunchKernelGGL((k_step_ahead<T, M, false, kShaped, kPayload>), g, b, 0, s, L);
+                hipLaunchKernelGGL((k_step_ahead<T, M, false, kShaped, kFins, kPayload, false>), g, b, 0, s, L);
             return;
         }
     }

@@ -524,3 +524,84 @@ def test_two_wave_launches_equal_the_one_wave_form(n, K, precision, make):
         np.testing.assert_allclose(getattr(stats, f)[0], getattr(ref, f)[0], rtol=1e-4)
     assert stats.n_nonfinite[0] == ref.n_nonfinite[0] == 0
     b.close()
+
+
+@pytest.mark.parametrize("make", ["plain", "shaped", "rudder", "payload", "persistent"])
+@pytest.mark.parametrize("n,K,n_steps", [(70, 2, 7), (130, 16, 100), (70, 5, 4), (66000, 3, 17), (100, 4097, 4100),
+                                         (65, 7, 8200)])
+def test_captured_chunks_equal_their_launches(n, K, n_steps, make):
+    """A captured chunk, which joins its K-step stretches in launches of up to 4096 steps, against
+    the K-step launches it stands for: states and the last launch's statistics. The attitudes
+    start off the unit sphere, so that the drift checks of the first stretches renormalise."""
+    import torch as t
+    base = synth.plain_class()
+    classes = {"plain": [base], "shaped": [synth.propeller_variants(base)], "rudder": [synth.rudder_class()],
+               "payload": [synth.payload_class()], "persistent": [base, synth.hetero_classes()[4]]}[make]
+    w = synth.mixed(classes, [n] + [40] * (len(classes) - 1))
+    got = []
+    for captured in (True, False):
+        b = make_batch(w)
+        if make == "persistent":
+            b.set_shape(mgx.LAUNCH_PERSISTENT, K, 256, 2)
+        x = [np.array(s) for s in b.unpack_state(b.get_state().cpu().numpy())]
+        for s in x:
+            s[3:7] *= 1.2
+        b.set_state(t.tensor(b.pack_state(x), dtype=b.dtype, device=b.device))
+        acts = b.gen_actions((n_steps + 9) // 10, seed=4)
+        if captured:
+            b.capture(acts, n_steps, K, hold=10, flags=mgx.STEP_STATS).replay()
+        else:
+            for k in range(0, n_steps, K):
+                b.step(acts, min(K, n_steps - k), hold=10, flags=mgx.STEP_STATS)
+        s = b.stats()
+        got.append((b.get_state(), b.t, [(s.step, s.n_renorm64[c], s.n_nonfinite[c], s.max_speed[c], s.max_qdrift[c])
+                                         for c in range(len(classes))]))
+        assert b.check() == (0, 0)
+        b.close()
+    assert t.equal(got[0][0], got[1][0])
+    assert got[0][1:] == got[1][1:]
+
+
+def fins_class(m):
+    """A rudder vehicle with m actuators: propellers first and last, four fins between them."""
+    from dataclasses import replace
+    c = synth.rudder_class()
+    extra = m - 5
+    add = lambda x, v: None if x is None else np.concatenate([x, np.repeat(np.asarray(v)[None], extra, 0)])  # noqa: E731
+    return replace(c, m=m, r=add(c.r, [0.1, 0.2, 0.05]), e=add(c.e, [0.0, 0.6, 0.8]), k=add(c.k, 21.0),
+                   tau=add(c.tau, 0.125), deadzone=add(c.deadzone, 0.0625), kind=add(c.kind, np.int32(0)),
+                   span=add(c.span, [0.0, 0.0, 1.0]), fin_max=add(c.fin_max, 0.0), fin_lift=add(c.fin_lift, 0.0),
+                   fin_drag0=add(c.fin_drag0, 0.0), fin_drag=add(c.fin_drag, 0.0))
+
+
+@pytest.mark.parametrize("m,payload", [(5, False), (8, False), (8, True)])
+@pytest.mark.parametrize("n,K", [(1, 4), (65, 33), (33090, 7)])
+def test_two_wave_fin_launches_equal_the_one_wave_form(n, K, m, payload):
+    """Classes with fins, whose low-order attitude words end with a launch: environments 0 ..
+    n - 1 of a batch small enough for two waves per tile against the same environments of one
+    too large for it, states, trajectories and wrenches bit for bit."""
+    import torch as t
+    from dataclasses import replace
+    cls = fins_class(m)
+    if payload:
+        cls = replace(cls, rg=np.array([0.015625, -0.0078125, 0.015625]))
+    big, got = 65600, []
+    for count in (n, big):
+        w = synth.mixed([cls], [count], steps=K, hold=3)
+        b = make_batch(w)
+        acts = b.gen_actions((K + 2) // 3 + 1, seed=4)
+        L = b.layout
+        traj = t.zeros((K, L.state_elems), device=b.device)
+        forces = t.zeros((K, L.force_row_elems), device=b.device)
+        s0 = b.get_state()
+        b.step(acts, K, hold=3)
+        plain = b.get_state()
+        b.set_state(s0)
+        b.t = 0
+        b.step(acts, K, hold=3, traj=traj, forces=forces)
+        assert t.equal(b.get_state(), plain) and b.check() == (0, 0)
+        got.append((b.unpack_state(plain)[0][:, :n].cpu(), traj.view(K, 13 + m, -1)[:, :, :n].cpu(),
+                    b.unpack_forces(forces)[0][:, :, :n].cpu()))
+        b.close()
+    for x, y in zip(*got):
+        assert t.equal(x, y)
