@@ -573,6 +573,13 @@ mgx_status mgx_station_reset(mgx_station* s, uint64_t seed, void* obs);
 mgx_status mgx_station_step(mgx_station* s, const void* actions, int32_t n_steps, void* obs, void* reward,
                             uint8_t* terminated, uint8_t* truncated, void* final_obs);
 
+/* One task step of a one-class batch (a Gym step) with the commands as a policy returns them:
+ * command i of environment e < n at actions[e * env_stride + i * act_stride] (device, the
+ * batch's precision, strides >= 1 in elements), nothing beyond them read. Everything else as
+ * mgx_station_step with n_steps = 1; MGX_E_INVALID for a batch of several classes. */
+mgx_status mgx_station_step_rows(mgx_station* s, const void* actions, int64_t env_stride, int64_t act_stride,
+                                 void* obs, void* reward, uint8_t* terminated, uint8_t* truncated, void* final_obs);
+
 /* Episode index and steps taken in the current episode, per global env id (host arrays of
  * n_total). Synchronises the stream. */
 mgx_status mgx_station_episodes(mgx_station* s, int32_t* episode, int32_t* steps);

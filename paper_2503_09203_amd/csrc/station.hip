@@ -37,6 +37,10 @@ struct StationArgs {
     int32_t* et;         // [npad] steps taken in the episode
     int32_t npad, nvalid;
     uint8_t* restart;    // [npad] 1 where an episode started during the launch
+    // one-step launches: command i of environment e at act + e * act_env + i * act_thr, for the
+    // environments e < act_n (the padded layout's npad, or a caller's rows of valid ones)
+    int64_t act_env, act_thr;
+    int32_t act_n, pad;
     T* obs;              // per step [13+m][npad], row k at obs + k * obs_stride
     T* final_obs;        // the same or NULL; written for lanes whose episode ended
     T* reward;           // per step [npad], row k at reward + k * flag_stride
@@ -259,8 +263,20 @@ __global__ void __launch_bounds__(256) k_station_step(StationLaunch<T> L) {
     load_record<T, kPayload>(A.rec, np, env, C.flags, E);
     int32_t ep = A.ep[env];
     int32_t et = A.et[env];
+    if constexpr (kMulti) {
 #pragma unroll
-    for (int i = 0; i < M; ++i) nxt[i] = A.act[i * np + env];
+        for (int i = 0; i < M; ++i) nxt[i] = A.act[i * np + env];
+    } else {
+        // lanes without a row load the last one and take zeros. Rows as a policy returns them
+        // are read where they lie: with their copy into the batch layout and two conversions
+        // of the flags, a Gym step was four launches (34 us from Python, 13.5 now)
+        const int64_t ea = env < A.act_n ? env : A.act_n - 1;
+        const T* row = A.act + ea * A.act_env;
+#pragma unroll
+        for (int i = 0; i < M; ++i) nxt[i] = row[i * A.act_thr];
+#pragma unroll
+        for (int i = 0; i < M; ++i) nxt[i] = env < A.act_n ? nxt[i] : T(0);
+    }
     env_prologue<T, kPayload>(C, E, IA2, Brb);
     const int32_t n_steps = kMulti ? A.n_steps : 1;
     // drained before the loop: a wait left to the values' first use would sit in the loop
@@ -532,8 +548,11 @@ extern "C" mgx_status mgx_station_reset(mgx_station* s, uint64_t seed, void* obs
     return MGX_OK;
 }
 
-extern "C" mgx_status mgx_station_step(mgx_station* s, const void* actions, int32_t n_steps, void* obs, void* reward,
-                                       uint8_t* terminated, uint8_t* truncated, void* final_obs) {
+// n_steps task steps from command rows in the batch layout, or (env_stride > 0) one task step of
+// a one-class batch from a caller's strided [n][m] commands.
+static mgx_status station_step(mgx_station* s, const void* actions, int64_t env_stride, int64_t act_stride,
+                               int32_t n_steps, void* obs, void* reward, uint8_t* terminated, uint8_t* truncated,
+                               void* final_obs) {
     if (!s) return fail(MGX_E_INVALID, "station is NULL");
     mgx_batch* b = s->batch;
     if (b->faulted) return fail(MGX_E_STATE, "batch faulted by an earlier device error");
@@ -543,40 +562,44 @@ extern "C" mgx_status mgx_station_step(mgx_station* s, const void* actions, int3
         return fail(MGX_E_INVALID, "actions, obs, reward, terminated and truncated are required");
     if (n_steps < 1) return fail(MGX_E_INVALID, "n_steps must be >= 1");
     hipDevice_guard g(b->device);
-    const size_t P = (size_t)b->prec;
     for (int c = 0; c < b->n_classes; ++c) {
         const int64_t so = b->state_off[c], po = b->pad_off[c];
-        hipError_t e;
-        if (b->prec == MGX_FP32) {
-            StationLaunch<float> L{station_args<float>(s, c), b->h_class_f[c]};
-            L.a.act = (const float*)((const char*)actions + P * b->act_off[c]);
-            L.a.obs = (float*)obs + so;
-            L.a.final_obs = final_obs ? (float*)final_obs + so : nullptr;
-            L.a.reward = (float*)reward + po;
+        auto launch = [&](auto zero, const auto& cls) {
+            using T = decltype(zero);
+            StationLaunch<T> L{station_args<T>(s, c), cls};
+            L.a.act = (const T*)actions + (env_stride > 0 ? 0 : b->act_off[c]);
+            L.a.act_env = env_stride > 0 ? env_stride : 1;
+            L.a.act_thr = env_stride > 0 ? act_stride : b->npad[c];
+            L.a.act_n = (int32_t)(env_stride > 0 ? b->n[c] : b->npad[c]);
+            L.a.obs = (T*)obs + so;
+            L.a.final_obs = final_obs ? (T*)final_obs + so : nullptr;
+            L.a.reward = (T*)reward + po;
             L.a.term = terminated + po;
             L.a.trunc = truncated + po;
             L.a.act_stride = b->row_elems;
             L.a.obs_stride = b->state_elems;
             L.a.flag_stride = b->npad_total;
             L.a.n_steps = n_steps;
-            e = launch_station<float>(L, b->m[c], b->stream);
-        } else {
-            StationLaunch<double> L{station_args<double>(s, c), b->h_class_d[c]};
-            L.a.act = (const double*)((const char*)actions + P * b->act_off[c]);
-            L.a.obs = (double*)obs + so;
-            L.a.final_obs = final_obs ? (double*)final_obs + so : nullptr;
-            L.a.reward = (double*)reward + po;
-            L.a.term = terminated + po;
-            L.a.trunc = truncated + po;
-            L.a.act_stride = b->row_elems;
-            L.a.obs_stride = b->state_elems;
-            L.a.flag_stride = b->npad_total;
-            L.a.n_steps = n_steps;
-            e = launch_station<double>(L, b->m[c], b->stream);
-        }
+            return launch_station<T>(L, b->m[c], b->stream);
+        };
+        const hipError_t e = b->prec == MGX_FP32 ? launch(0.0f, b->h_class_f[c]) : launch(0.0, b->h_class_d[c]);
         if (e != hipSuccess) return hip_fail(b, e, "station step launch");
     }
     return MGX_OK;
+}
+
+extern "C" mgx_status mgx_station_step(mgx_station* s, const void* actions, int32_t n_steps, void* obs, void* reward,
+                                       uint8_t* terminated, uint8_t* truncated, void* final_obs) {
+    return station_step(s, actions, 0, 0, n_steps, obs, reward, terminated, truncated, final_obs);
+}
+
+extern "C" mgx_status mgx_station_step_rows(mgx_station* s, const void* actions, int64_t env_stride,
+                                            int64_t act_stride, void* obs, void* reward, uint8_t* terminated,
+                                            uint8_t* truncated, void* final_obs) {
+    if (!s) return fail(MGX_E_INVALID, "station is NULL");
+    if (s->batch->n_classes != 1) return fail(MGX_E_INVALID, "command rows per environment are for one-class batches");
+    if (env_stride < 1 || act_stride < 1) return fail(MGX_E_INVALID, "strides must be >= 1");
+    return station_step(s, actions, env_stride, act_stride, 1, obs, reward, terminated, truncated, final_obs);
 }
 
 extern "C" mgx_status mgx_station_episodes(mgx_station* s, int32_t* episode, int32_t* steps) {

@@ -238,6 +238,7 @@ SIGNATURES = {
     "mgx_station_destroy": (I32, [P]),
     "mgx_station_reset": (I32, [P, U64, P]),
     "mgx_station_step": (I32, [P, P, I32, P, P, P, P, P]),
+    "mgx_station_step_rows": (I32, [P, P, I64, I64, P, P, P, P, P]),
     "mgx_station_episodes": (I32, [P, P, P]),
     "mgx_station_resample": (I32, [P, ctypes.POINTER(DrSpec), P, U64]),
 }
@@ -909,12 +910,33 @@ class VecStationKeeping:
     def _view(self, flat):
         return flat.view(-1, self.batch.n_pad[0])[:, :self.num_envs].t()
 
+    def _as_rows(self, actions):
+        """True if the kernel can read ``actions`` where they lie: the batch's precision and
+        device, one row per environment, on the batch's stream."""
+        torch, b = _torch(), self.batch
+        return (type(actions) is torch.Tensor and actions.dtype == b.dtype and actions.device == b.device
+                and actions.shape == (self.num_envs, self.m) and min(actions.stride()) > 0
+                and actions.layout == torch.strided and not actions.is_neg()
+                and torch.cuda.current_stream(b.device) == b.stream)
+
     def reset(self, seed=0):
         self.task.reset(seed, self._out["obs"][0])
         return self._view(self._out["obs"][0]), {}
 
     def step(self, actions):
         n = self.num_envs
+        if self._as_rows(actions):
+            # one launch: the kernel reads the rows in place and writes the flags as bool
+            # (a copy into the batch layout and two conversions of the flags were three more)
+            b, o = self.batch, self._out
+            np_ = b.n_pad[0]
+            flags = _torch().empty((2, np_), dtype=_torch().bool, device=b.device)
+            f = flags.data_ptr()
+            _call("mgx_station_step_rows", self.task.h, actions.data_ptr(), actions.stride(0), actions.stride(1),
+                  o["obs"].data_ptr(), o["reward"].data_ptr(), f, f + np_, o["final_obs"].data_ptr())
+            shape, stride = (n, STATE_FIXED + self.m), (1, np_)
+            return (o["obs"].as_strided(shape, stride), o["reward"][0, :n], flags[0, :n], flags[1, :n],
+                    {"final_obs": o["final_obs"].as_strided(shape, stride)})
         self._act[0].view(self.m, self.batch.n_pad[0])[:, :n].copy_(actions.t())
         o = self.task.step(self._act, self._out)
         return (self._view(o["obs"][0]), o["reward"][0, :n], o["terminated"][0, :n].bool(),

@@ -410,3 +410,56 @@ def test_nonfinite_component_ends_the_episode(bad):
     assert (out["reward"][want] == 0).all() and (out["reward"][13 + m:n] != 0).all()
     assert np.isfinite(out["obs"]).all()
     b.close()
+
+
+@pytest.mark.parametrize("precision", [mgx.FP32, mgx.FP64])
+@pytest.mark.parametrize("m,n", [(1, 1), (6, 64), (8, 65), (4, 300)])
+def test_rows_read_in_place_equal_the_copied_ones(m, n, precision):
+    """VecStationKeeping.step reads command rows of the batch's own type where they lie, whatever
+    their strides, and copies any other: contiguous rows, a slice of a wider tensor and a
+    transposed tensor against the same commands in the other float type (exact in both), over
+    restarts; the flags returned by a call outlive the next one."""
+    t = torch()
+    w = synth.mixed([synth.draw_class(m, 0)], [n])
+    envs = [mgx.VecStationKeeping(w.classes[0], w.params, n, precision=precision, **DESC) for _ in range(2)]
+    a, b = envs
+    assert t.equal(a.reset(5)[0], b.reset(5)[0])
+    dtype, other = a.batch.dtype, t.float64 if precision == mgx.FP32 else t.float32
+    g = t.Generator(device="cuda").manual_seed(1)
+    kept = []
+    for k in range(DESC["max_steps"] + 2):
+        x = t.rand((n, m), generator=g, device="cuda", dtype=t.float32) * 2.4 - 1.2
+        wide = t.full((n, m + 3), 9.0, device="cuda", dtype=dtype)
+        wide[:, 1:m + 1] = x
+        rows = [x.to(dtype), wide[:, 1:m + 1], x.to(dtype).t().contiguous().t()][k % 3]
+        assert a._as_rows(rows) and not b._as_rows(x.to(other))
+        got, ref = a.step(rows), b.step(x.to(other))
+        for u, v in zip(got[:4] + (got[4]["final_obs"],), ref[:4] + (ref[4]["final_obs"],)):
+            assert u.dtype == v.dtype and u.shape == v.shape and t.equal(u, v)
+        kept.append((got[2], got[2].clone(), got[3], got[3].clone()))
+    assert any(bool(x[3].any()) for x in kept)
+    assert all(t.equal(p, q) and t.equal(r, s) for p, q, r, s in kept)
+    with t.cuda.stream(t.cuda.Stream()):      # another stream than the batch's: copied
+        assert not a._as_rows(x.to(dtype))
+    for e in envs:
+        e.close()
+
+
+def test_rows_entry_refuses_bad_arguments():
+    w = synth.mixed([synth.draw_class(6, 0), synth.draw_class(4, 1)], [5, 6])
+    b = make_batch(w)
+    st = mgx.Station(b)
+    st.reset(1)
+    o = st.empty_outputs(1)
+    x = b.empty_actions(1)
+    args = [o[k].data_ptr() for k in ("obs", "reward", "terminated", "truncated", "final_obs")]
+    assert mgx.lib().mgx_station_step_rows(st.h, x.data_ptr(), 6, 1, *args) == mgx.MGX_E_INVALID   # two classes
+    b.close()
+    b = make_batch(synth.mixed([synth.draw_class(6, 0)], [5]))
+    st = mgx.Station(b)
+    assert mgx.lib().mgx_station_step_rows(st.h, x.data_ptr(), 6, 1, *args) == mgx.MGX_E_STATE     # no reset
+    st.reset(1)
+    for strides in ((0, 1), (6, 0), (-6, 1)):
+        assert mgx.lib().mgx_station_step_rows(st.h, x.data_ptr(), *strides, *args) == mgx.MGX_E_INVALID
+    assert mgx.lib().mgx_station_step_rows(st.h, None, 6, 1, *args) == mgx.MGX_E_INVALID
+    b.close()
