@@ -163,24 +163,24 @@ __device__ __forceinline__ int32_t write_record(const double inertia[3], double 
     return flags;
 }
 
+// Normals 2 j and 2 j + 1 of the seeded initial state of global env id g (Box-Muller over
+// Philox words, in double).
+__device__ __forceinline__ void seeded_normals(uint64_t g, uint64_t seed, int j, double& z0, double& z1) {
+    uint32_t c[4] = {(uint32_t)g, 0u, (uint32_t)j, 0u};
+    philox4x32_10(c, (uint32_t)seed, kStreamInit << 24);
+    const double u0 = u53(c[0], c[1]), u1 = u53(c[2], c[3]);
+    const double rad = sqrt(-2.0 * log(1.0 - u0));
+    const double ang = 2.0 * M_PI * u1;
+    z0 = rad * cos(ang);
+    z1 = rad * sin(ang);
+}
+
 // Seeded initial state of global env id g: p = 0, q uniform on S^3 (normalised Gaussian),
-// nu ~ N(0, 0.2^2), n = 0; Box-Muller over Philox words, in double, rounded once.
+// nu ~ N(0, 0.2^2), n = 0; in double, rounded once.
 template <typename T>
 __device__ __forceinline__ void seeded_state(uint64_t g, uint64_t seed, int m, T* state, int64_t npad, int64_t e) {
-    double u[10];
-    for (int j = 0; j < 5; ++j) {
-        uint32_t c[4] = {(uint32_t)g, 0u, (uint32_t)j, 0u};
-        philox4x32_10(c, (uint32_t)seed, kStreamInit << 24);
-        u[2 * j] = u53(c[0], c[1]);
-        u[2 * j + 1] = u53(c[2], c[3]);
-    }
     double z[10];
-    for (int j = 0; j < 5; ++j) {
-        double rad = sqrt(-2.0 * log(1.0 - u[2 * j]));
-        double ang = 2.0 * M_PI * u[2 * j + 1];
-        z[2 * j] = rad * cos(ang);
-        z[2 * j + 1] = rad * sin(ang);
-    }
+    for (int j = 0; j < 5; ++j) seeded_normals(g, seed, j, z[2 * j], z[2 * j + 1]);
     double qn = sqrt(z[0] * z[0] + z[1] * z[1] + z[2] * z[2] + z[3] * z[3]);
     for (int j = 0; j < 3; ++j) state[j * npad + e] = (T)0;
     for (int j = 0; j < 4; ++j) state[(3 + j) * npad + e] = (T)(z[j] / qn);

@@ -172,3 +172,34 @@ def test_resample_rebuilds_payload_records():
     x, _, _ = oracle.rollout(envs, x, oracle.pack_actions(acts[0]), 10, 32)
     assert component_errors(got, oracle.unpack_state(x, c.m)).max() <= 1e-4
     b.close()
+
+
+@pytest.mark.parametrize("make", ["plain", "payload"])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 200])
+def test_tiles_draw_alike_for_lists_and_whole_batches(n, make):
+    """Draws and seeded states in tiles of 64: a shuffled list of every environment gives the
+    records and states of the whole batch, and a record is the one the parameter upload builds
+    from the drawn values, bit for bit."""
+    t = torch()
+    cls = synth.payload_class() if make == "payload" else synth.plain_class()
+    nominal = nominal_of(cls)[None]
+    ids = np.random.default_rng(1).permutation(n)
+    out = []
+    for which in (None, ids):
+        cid = [mgx.mgx_class_define(cls)]
+        plan = mgx.mgx_batch_plan(cid, [n], 0.01, mgx.FP64)
+        rec = t.zeros(plan.record_elems, dtype=t.float64, device="cuda")
+        b = mgx.Batch([cls], [n], 0.01, mgx.FP64, record=rec)
+        b.resample(SPEC, nominal, seed=9, epoch=1)
+        b.resample(SPEC, nominal, env_ids=which, seed=9, epoch=2)
+        b.reset(seed=4)
+        if which is not None:
+            b.reset(seed=5)
+            b.reset(env_ids=which, seed=4)
+        out.append((rec.clone(), b.get_state()))
+        drawn = b.get_params()
+        b.set_params(synth.EnvParams(**drawn))
+        assert t.equal(rec, out[-1][0])
+        assert b.check() == (0, 0)
+        b.close()
+    assert t.equal(out[0][0], out[1][0]) and t.equal(out[0][1], out[1][1])
