@@ -145,13 +145,18 @@ __device__ __forceinline__ void recompute_segment(const AdjArgs& A, const ClassT
     RowCursor rc(A, A.t0 + k0);
     T a[M], nxt[M];
     load_action<T, M>(A, rc.row, e, nxt);
-    for (int k = k0; k < k1; ++k) {
-        uint32_t pass = 0;
+    __builtin_amdgcn_s_waitcnt(0);
+    uint32_t pass = 0;
+    auto take = [&]() {
+        pass = 0;
 #pragma unroll
         for (int i = 0; i < M; ++i) {
             pass |= (nxt[i] > T(-1) && nxt[i] < T(1)) ? 1u << i : 0u;
             a[i] = clip1(nxt[i]);
         }
+    };
+    take();
+    for (int k = k0; k < k1; ++k) {
         load_action<T, M>(A, k + 1 < k1 ? rc.next_row() : rc.row, e, nxt);
         rc.advance();
         store_state<T, M>(seg_row_of<T, M>(A, tile, seg, k), kWave, lane, s);
@@ -160,6 +165,10 @@ __device__ __forceinline__ void recompute_segment(const AdjArgs& A, const ClassT
         T* tr = tape_row_of<T>(A, tile, seg, k);
         store_tape<T, M>(tr, kWave, lane, tp);
         tr[kTapeLen * kWave + lane] = T(pass);
+        // taken at the step's end: vector memory operations complete in order, so this waits
+        // for the stores of the step before, and not (as at the top of the next step, where
+        // the compiler cannot count them) for those just issued
+        take();
     }
 }
 
@@ -190,7 +199,7 @@ __global__ void __launch_bounds__(128) k_rollout_fwd(AdjArgs A, ClassT<T> Cs) {
         Brb[j] = E.buoy * C.rb[j];
     }
     T* ck = (T*)A.ckpt_buf;
-    const int seg_last = (A.H - 1) / A.ckpt, k_last = seg_last * A.ckpt;
+    const int seg_last = (A.H - 1) / A.ckpt;
     if (role == 1) {
         __syncthreads();
         recompute_segment<T, M, kShaped>(A, C, E, IA2, Brb, e, lane, seg_last);
@@ -199,27 +208,41 @@ __global__ void __launch_bounds__(128) k_rollout_fwd(AdjArgs A, ClassT<T> Cs) {
     T* pos = (T*)A.pos;
     StateT<T, M> s;
     load_state<T, M>((const T*)A.state, np, e, s);
-    // The action row of step k + 1 is in flight while step k runs (with per-step actions a
-    // load issued right before its use would leave every step waiting on memory).
+    // The action rows of the next kAhead steps are in flight while a step runs, each in its own
+    // buffer (the loop takes kAhead steps per turn): rows come from HBM, further away than a
+    // step takes (8192 x 256 with 8 thrusters: 190 us with one row ahead, 173 with four). A
+    // wait counts the operations behind it on the shortest way there, so of four rows about two
+    // stay in flight behind their steps' position stores.
+    constexpr int kAhead = 4;
     RowCursor rc(A, A.t0);
-    T a[M], nxt[M];
-    load_action<T, M>(A, rc.row, e, nxt);
-    auto step = [&](int k) {
+    T row[kAhead][M];
+    auto fetch = [&](T r[M], int k) {
+        load_action<T, M>(A, rc.row, e, r);
+        if (k + 1 < A.H) rc.advance();  // past the end the last row is fetched again
+    };
 #pragma unroll
-        for (int i = 0; i < M; ++i) a[i] = clip1(nxt[i]);
-        load_action<T, M>(A, k + 1 < A.H ? rc.next_row() : rc.row, e, nxt);
-        rc.advance();
+    for (int u = 0; u < kAhead; ++u) fetch(row[u], u);
+    int seg = 0, next_ckpt = 0;
+    auto step = [&](T r[M], int k) {
+        if (k == next_ckpt) {
+            store_state<T, M>(ck + (int64_t)seg * A.ckpt_stride, np, e, s);
+            if (seg == seg_last) __syncthreads();  // wave 1 starts from this checkpoint
+            ++seg;
+            next_ckpt += A.ckpt;
+        }
+        T a[M];
+#pragma unroll
+        for (int i = 0; i < M; ++i) a[i] = clip1(r[i]);
+        fetch(r, k + kAhead);
         step_body<T, M, false, kShaped>(C, E, IA2, Brb, s, a);
 #pragma unroll
         for (int j = 0; j < 3; ++j) pos[(int64_t)k * A.pos_stride + j * np + e] = s.p[j];
     };
-    for (int k = 0; k < k_last; ++k) {
-        if (k % A.ckpt == 0) store_state<T, M>(ck + (int64_t)(k / A.ckpt) * A.ckpt_stride, np, e, s);
-        step(k);
+    for (int k = 0; k < A.H; k += kAhead) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            if (k + u < A.H) step(row[u], k + u);
     }
-    store_state<T, M>(ck + (int64_t)seg_last * A.ckpt_stride, np, e, s);
-    __syncthreads();
-    for (int k = k_last; k < A.H; ++k) step(k);
     store_state<T, M>((T*)A.state, np, e, s);
 }
 

@@ -209,3 +209,39 @@ def test_classes_in_one_batch_match_each_class_alone():
         assert np.array_equal(both["gp"][:, sl], alone["gp"]), f"parameter gradients of class {c}"
         assert np.abs(alone["gp"]).max() > 0 and np.abs(alone["ga"][0]).max() > 0
         off += ns[c]
+
+
+@pytest.mark.parametrize("H_,hold,ckpt,n,precision", [
+    (1, 1, 32, 64, mgx.FP32), (3, 1, 1, 70, mgx.FP32), (5, 8, 4, 64, mgx.FP32), (33, 1, 32, 130, mgx.FP32),
+    (64, 3, 32, 64, mgx.FP32), (67, 5, 7, 70, mgx.FP64)])
+def test_forward_rows_ahead_at_their_edges(H_, hold, ckpt, n, precision):
+    """The forward pass keeps four action rows in flight: horizons below, at and past
+    multiples of four, holds, and checkpoints at every phase. Positions are those of single
+    steps and gradients those of one segment, bit for bit (the same operations in the same
+    order, so no tolerance)."""
+    t = torch()
+    from paper_2503_09203_amd.autograd import DiffRollout
+    w = synth.differentiable(n=n, horizon=H_)
+    rows = -(-H_ // hold)
+    acts_np = w.actions(H_)[0][:rows]
+    b = mgx.Batch(w.classes, w.n_envs, w.dt, precision)
+    init = t.tensor(b.pack_state([w.state[0].stacked()]), dtype=b.dtype, device=b.device)
+    f = lambda x: t.tensor(np.ascontiguousarray(x), dtype=t.float64, device=b.device, requires_grad=True)
+    out = []
+    for c in (ckpt, H_):
+        a = t.tensor(b.pack_actions([acts_np]), dtype=b.dtype, device=b.device, requires_grad=True)
+        par = f(w.params.dlin), f(w.params.dquad), f(w.params.added)
+        ro = DiffRollout(b, w.params, init, H_, hold=hold, ckpt=c)
+        pos = ro.positions(ro(a, *par))
+        (pos * pos).sum().backward()
+        out.append([x.cpu().numpy() for x in (pos.detach(), a.grad, *(p.grad for p in par))])
+    for x, y in zip(*out):
+        assert np.array_equal(x, y)
+    assert np.abs(out[0][1]).max() > 0
+    b.set_state(init)
+    b.t = 0
+    for k in range(H_):
+        b.step(a.detach(), 1, hold=hold)
+        p = b.unpack_state(b.get_state().cpu().numpy())[0][:3]
+        assert np.array_equal(out[0][0][k], p), k
+    b.close()
