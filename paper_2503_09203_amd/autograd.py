@@ -33,16 +33,14 @@ class DiffRollout:
         self.init = init_state
         L = batch.layout
         npad_tot = L.n_pad_total
-        # index maps from (padded, class-segmented) layouts to class-concatenated env order
-        pos_idx, par_idx = [], []
+        # index map from the (padded, class-segmented) layout to class-concatenated env order
+        par_idx = []
         pad_off = 0
         for c in range(len(batch.m)):
             npad, n = batch.n_pad[c], batch.n[c]
             e = np.arange(n)
-            pos_idx.append(np.stack([3 * pad_off + j * npad + e for j in range(3)]))
             par_idx.append(np.stack([18 * pad_off + j * npad + e for j in range(18)]))
             pad_off += npad
-        self.pos_idx = torch.as_tensor(np.concatenate(pos_idx, axis=1), device=dev)   # [3, N]
         self.par_idx = torch.as_tensor(np.concatenate(par_idx, axis=1), device=dev)   # [18, N]
         self.pos_row = 3 * npad_tot
         self.par_len = 18 * npad_tot
@@ -54,8 +52,14 @@ class DiffRollout:
         mgx.mgx_batch_set_params(self.b.h, ptrs, 1)
 
     def positions(self, pos):
-        """[H, 3 * n_pad_total] -> [H, 3, N] (differentiable gather)."""
-        return pos[:, self.pos_idx]
+        """[H, 3 * n_pad_total] -> [H, 3, N] (differentiable). The classes' segments are
+        sliced and joined: an index gather's backward sorts the indices and adds them up one by
+        one (8192 environments, 256 steps: 990 us for forward and backward, 840 so)."""
+        parts, off = [], 0
+        for n, npad in zip(self.b.n, self.b.n_pad):
+            parts.append(pos[:, off:off + 3 * npad].unflatten(1, (3, npad))[:, :, :n])
+            off += 3 * npad
+        return torch.cat(parts, dim=2)
 
     def __call__(self, actions, dlin, dquad, added):
         return RolloutFunction.apply(actions, dlin, dquad, added, self)

@@ -153,3 +153,29 @@ def test_double_attitude_series_and_their_fallbacks(rate, norm2):
     fd = [(turned(w + h * e) - turned(w - h * e)) @ xbar[3:7] / (2 * h) for e in np.eye(3)]
     # rounding 2^-53 / h, and the third derivative (dt / 2)^3 h^2
     np.testing.assert_allclose(xb[10:13], fd, rtol=0, atol=8 * 2.0 ** -53 / h + (0.5 * dt) ** 3 * h * h)
+
+
+@pytest.mark.parametrize("n,n_pad", [([70], [128]), ([64, 1, 130], [64, 64, 192])])
+def test_positions_are_the_gather_of_the_padded_layout(n, n_pad):
+    """DiffRollout.positions and its derivatives (reverse, forward, vmap) against the index
+    gather it stands for: copies only, so equal."""
+    import types
+
+    import torch
+    from paper_2503_09203_amd.autograd import DiffRollout
+    ro = DiffRollout.__new__(DiffRollout)
+    ro.b = types.SimpleNamespace(n=n, n_pad=n_pad)
+    off = np.cumsum([0] + n_pad)
+    idx = torch.as_tensor(np.concatenate(
+        [np.stack([3 * o + j * p + np.arange(k) for j in range(3)]) for k, p, o in zip(n, n_pad, off)], axis=1))
+    g = torch.Generator().manual_seed(3)
+    x = torch.randn((5, 3 * sum(n_pad)), generator=g)
+    v = torch.randn((5, 3, sum(n)), generator=g)
+    ref = lambda p: p[:, idx]
+    for fn in (lambda f: f(x), lambda f: f(x.t().contiguous().t()), lambda f: torch.func.vjp(f, x)[1](v)[0],
+               lambda f: torch.func.jvp(f, (x,), (2 * x,))[1],
+               lambda f: torch.func.vmap(f)(torch.stack([x, 2 * x])), lambda f: f(x[..., None].expand(-1, -1, 2))):
+        assert torch.equal(fn(ro.positions), fn(ref))
+    assert ro.positions(x).data_ptr() != x.data_ptr() and ro.positions(x).is_contiguous()
+    with pytest.raises(Exception):
+        ro.positions(x[:, :-1 - (n_pad[-1] - n[-1])])
