@@ -133,10 +133,11 @@ __device__ __forceinline__ T* tape_row_of(const AdjArgs& A, int64_t tile, int se
 // it: each step's state before the step into the recompute buffer, and its forward
 // quantities and the actions' clip mask into the tape. Used by the forward pass for the last
 // segment and by the backward for the others; the actions of step k + 1 are in flight while
-// step k runs.
-template <typename T, int M, bool kShaped>
+// step k runs. `after(k)` is called at the end of step k.
+template <typename T, int M, bool kShaped, typename After>
 __device__ __forceinline__ void recompute_segment(const AdjArgs& A, const ClassT<T>& C, const EnvT<T>& E,
-                                                  const T IA2[3], const T Brb[3], int64_t e, int lane, int seg) {
+                                                  const T IA2[3], const T Brb[3], int64_t e, int lane, int seg,
+                                                  After after) {
     const int k0 = seg * A.ckpt;
     const int k1 = (k0 + A.ckpt < A.H) ? k0 + A.ckpt : A.H;
     const int64_t tile = e / kWave;
@@ -169,6 +170,7 @@ __device__ __forceinline__ void recompute_segment(const AdjArgs& A, const ClassT
         // for the stores of the step before, and not (as at the top of the next step, where
         // the compiler cannot count them) for those just issued
         take();
+        after(k);
     }
 }
 
@@ -202,7 +204,7 @@ __global__ void __launch_bounds__(128) k_rollout_fwd(AdjArgs A, ClassT<T> Cs) {
     const int seg_last = (A.H - 1) / A.ckpt;
     if (role == 1) {
         __syncthreads();
-        recompute_segment<T, M, kShaped>(A, C, E, IA2, Brb, e, lane, seg_last);
+        recompute_segment<T, M, kShaped>(A, C, E, IA2, Brb, e, lane, seg_last, [](int) {});
         return;
     }
     T* pos = (T*)A.pos;
@@ -246,6 +248,132 @@ __global__ void __launch_bounds__(128) k_rollout_fwd(AdjArgs A, ClassT<T> Cs) {
     store_state<T, M>((T*)A.state, np, e, s);
 }
 
+// The forward pass in three waves per tile (block of 192), for launches of few tiles. Wave 1
+// forms the thrust of the steps ahead and hands each step's wrench over in LDS, in groups of
+// kFwdGroup steps with one block barrier each (two buffers: it fills one while wave 0 reads
+// the other); wave 0 runs pose and velocity. Wave 1 stores the rotor states of the
+// checkpoints, wave 0 the rest and the positions. Once both have stored the last segment's
+// checkpoint, wave 2 runs that segment again as the backward's recomputation would, into the
+// recompute buffer and the tape, while the others finish it: the backward then sweeps the last
+// segment at once instead of first waiting for its recomputation. With a SIMD for each wave a
+// lone wave's issue rate (at most one instruction per four cycles) bounds the step, so the
+// split shortens it: 8192 x 256 with 8 thrusters 173 -> 127 us, in double 153 -> 113
+// for 128 steps.
+// Every wave reaches the same nb + 1 barriers, nb the number of groups: barrier g ends the
+// forming of group g and the reading of group g - 1.
+constexpr int kFwdGroup = 4;
+
+template <typename T, int M, bool kShaped>
+__global__ void __launch_bounds__(3 * kWave) k_rollout_fwd_ahead(AdjArgs A, ClassT<T> Cs) {
+    __shared__ T ring[2][kFwdGroup][6][kWave];
+    const int role = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t e = (int64_t)blockIdx.x * kWave + lane;
+    const ClassT<T> C = class_in_vgpr<T, M>(Cs);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (A.advance) A.misc->t[A.wr] = A.t0 + A.advance;
+        prepare_next_slot(A.misc, A.wr);
+    }
+    const int64_t np = A.npad;
+    T* ck = (T*)A.ckpt_buf;
+    const int nb = (A.H + kFwdGroup - 1) / kFwdGroup, seg_last = (A.H - 1) / A.ckpt;
+    int next_ckpt = 0;
+    if (role == 1) {
+        T* S = (T*)A.state + kStateFixed * np + e;
+        T* cn = ck + kStateFixed * np + e;
+        T n[M];
+#pragma unroll
+        for (int i = 0; i < M; ++i) n[i] = S[i * np];
+        // The action rows of the next group are in flight while a group is formed, each in its
+        // own buffer: rows come from HBM, further away than a step takes.
+        RowCursor rc(A, A.t0);
+        T row[kFwdGroup][M];
+        auto fetch = [&](T r[M], int k) {
+            load_action<T, M>(A, rc.row, e, r);
+            if (k + 1 < A.H) rc.advance();  // past the end the last row is fetched again
+        };
+#pragma unroll
+        for (int u = 0; u < kFwdGroup; ++u) fetch(row[u], u);
+        for (int g = 0; g < nb; ++g) {
+#pragma unroll
+            for (int u = 0; u < kFwdGroup; ++u) {
+                const int k = g * kFwdGroup + u;
+                if (k < A.H) {
+                    if (k == next_ckpt) {
+#pragma unroll
+                        for (int i = 0; i < M; ++i) cn[i * np] = n[i];
+                        cn += A.ckpt_stride;
+                        next_ckpt += A.ckpt;
+                    }
+                    T a[M], nl[M], x[6];
+#pragma unroll
+                    for (int i = 0; i < M; ++i) a[i] = clip1(row[u][i]);
+                    fetch(row[u], k + kFwdGroup);
+                    thrust_part<T, M, kShaped>(C, n, a, nl, x);
+#pragma unroll
+                    for (int j = 0; j < 6; ++j) ring[g & 1][u][j][lane] = x[j];
+#pragma unroll
+                    for (int i = 0; i < M; ++i) n[i] = nl[i];
+                }
+            }
+            __syncthreads();
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < M; ++i) S[i * np] = n[i];
+        return;
+    }
+    EnvT<T> E;
+    load_env<T>((const T*)A.rec, np, e, E);
+    set_amc(E, C.flags);
+    T IA2[3], Brb[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        IA2[j] = C.inertia[j] + E.A[3 + j];
+        Brb[j] = E.buoy * C.rb[j];
+    }
+    if (role == 2) {
+        // the group with the last checkpoint ends for wave 0 at the barrier after its own
+        const int start = seg_last * A.ckpt / kFwdGroup + 2;
+        for (int g = 0; g < start; ++g) __syncthreads();
+        int left = nb + 1 - start;
+        recompute_segment<T, M, kShaped>(A, C, E, IA2, Brb, e, lane, seg_last, [&](int k) {
+            if (k % kFwdGroup == 0 && left > 0) {
+                __syncthreads();
+                --left;
+            }
+        });
+        for (; left > 0; --left) __syncthreads();
+        return;
+    }
+    T* pos = (T*)A.pos + e;
+    RigidT<T> s;
+    load_rigid<T>((const T*)A.state, np, e, s);
+    for (int g = 0; g < nb; ++g) {
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kFwdGroup; ++u) {
+            const int k = g * kFwdGroup + u;
+            if (k < A.H) {
+                if (k == next_ckpt) {
+                    store_rigid<T>(ck, np, e, s);
+                    ck += A.ckpt_stride;
+                    next_ckpt += A.ckpt;
+                }
+                T x[6];
+#pragma unroll
+                for (int j = 0; j < 6; ++j) x[j] = ring[g & 1][u][j][lane];
+                rigid_part<T, M>(C, E, IA2, Brb, s, nullptr, x);
+#pragma unroll
+                for (int j = 0; j < 3; ++j) pos[j * np] = s.p[j];
+                pos += A.pos_stride;
+            }
+        }
+    }
+    __syncthreads();
+    store_rigid<T>((T*)A.state, np, e, s);
+}
+
 // Reverse sweep with per-segment recomputation. Two waves per 64-environment tile (block of
 // 128): wave 1 recomputes segment s - 1 from its checkpoint into one half of the segment
 // buffer while wave 0 sweeps segment s backwards from the other half, so recomputation
@@ -281,7 +409,7 @@ __global__ void __launch_bounds__(128) k_rollout_bwd(AdjArgs A, ClassT<T> Cs) {
     // the forward pass stored the last segment's states and tape
     if (role == 1) {
         for (int seg = nseg - 1; seg >= 0; --seg) {
-            if (seg > 0) recompute_segment<T, M, kShaped>(A, C, E, IA2, Brb, e, lane, seg - 1);
+            if (seg > 0) recompute_segment<T, M, kShaped>(A, C, E, IA2, Brb, e, lane, seg - 1, [](int) {});
             __syncthreads();
         }
         return;
@@ -398,17 +526,31 @@ __global__ void __launch_bounds__(128) k_rollout_bwd(AdjArgs A, ClassT<T> Cs) {
             return hipErrorInvalidValue; \
     }
 
+// Whether the three waves of every tile find a SIMD each. Up to there the three-wave forms are
+// faster (forward pass of 16,384 x 128 90 against 105 us, in double 89 against 98 for
+// 16,384 x 64); beyond, the SIMDs fill with whole tiles and the hand-over only adds work
+// (65,536 x 64: 168 against 149; in double 169 against 145 for 32,768 x 64).
+static bool wave_per_simd(int64_t npad, int n_cu) { return 3 * (npad / kWave) <= 4 * (int64_t)n_cu; }
+
 template <typename T>
-hipError_t launch_rollout_fwd(const AdjArgs& A, const ClassT<T>& C, int m, bool shaped, hipStream_t s) {
-    // one block of two waves per 64-environment tile (npad is a multiple of 64): a few
-    // thousand environments are a few tiles per class, each on a compute unit of its own
-    // (blocks of several tiles packed them onto fewer units, sharing their issue and memory
-    // pipelines: 0.180 against 0.171 ms at 8192 x 256 with 8 thrusters)
+hipError_t launch_rollout_fwd(const AdjArgs& A, const ClassT<T>& C, int m, bool shaped, int n_cu, hipStream_t s) {
+    // one block per 64-environment tile (npad is a multiple of 64): a few thousand
+    // environments are a few tiles per class, each on a compute unit of its own (blocks of
+    // several tiles packed them onto fewer units, sharing their issue and memory pipelines:
+    // 0.180 against 0.171 ms at 8192 x 256 with 8 thrusters and two waves per tile)
     if (A.npad % kWave != 0) return hipErrorInvalidValue;
-    const unsigned grid = (unsigned)(A.npad / kWave), block = 2 * kWave;
-#define KERNEL k_rollout_fwd
-    MGX_ADJ_SWITCH
+    const unsigned grid = (unsigned)(A.npad / kWave);
+    if (wave_per_simd(A.npad, n_cu)) {
+        const unsigned block = 3 * kWave;
+#define KERNEL k_rollout_fwd_ahead
+        MGX_ADJ_SWITCH
 #undef KERNEL
+    } else {
+        const unsigned block = 2 * kWave;
+#define KERNEL k_rollout_fwd
+        MGX_ADJ_SWITCH
+#undef KERNEL
+    }
     return hipGetLastError();
 }
 
@@ -423,8 +565,8 @@ hipError_t launch_rollout_bwd(const AdjArgs& A, const ClassT<T>& C, int m, bool 
     return hipGetLastError();
 }
 
-template hipError_t launch_rollout_fwd<float>(const AdjArgs&, const ClassT<float>&, int, bool, hipStream_t);
-template hipError_t launch_rollout_fwd<double>(const AdjArgs&, const ClassT<double>&, int, bool, hipStream_t);
+template hipError_t launch_rollout_fwd<float>(const AdjArgs&, const ClassT<float>&, int, bool, int, hipStream_t);
+template hipError_t launch_rollout_fwd<double>(const AdjArgs&, const ClassT<double>&, int, bool, int, hipStream_t);
 template hipError_t launch_rollout_bwd<float>(const AdjArgs&, const ClassT<float>&, int, bool, hipStream_t);
 template hipError_t launch_rollout_bwd<double>(const AdjArgs&, const ClassT<double>&, int, bool, hipStream_t);
 
@@ -579,9 +721,9 @@ static mgx_status rollout_forward(mgx_batch* b, const void* actions, int64_t n_r
         A.advance = (c == b->n_classes - 1) ? H : 0;
         hipError_t e;
         if (b->prec == MGX_FP32)
-            e = launch_rollout_fwd<float>(A, b->h_class_f[c], b->m[c], class_shaped(b, c), b->stream);
+            e = launch_rollout_fwd<float>(A, b->h_class_f[c], b->m[c], class_shaped(b, c), b->n_cu, b->stream);
         else
-            e = launch_rollout_fwd<double>(A, b->h_class_d[c], b->m[c], class_shaped(b, c), b->stream);
+            e = launch_rollout_fwd<double>(A, b->h_class_d[c], b->m[c], class_shaped(b, c), b->n_cu, b->stream);
         if (e != hipSuccess) return hip_fail(b, e, "rollout forward launch");
     }
     b->slot = 1 - b->slot;

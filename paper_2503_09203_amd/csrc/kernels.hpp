@@ -331,7 +331,7 @@ hipError_t launch_step(const StepLaunch<T>& L, int m, int block, int n_cu, hipSt
 template <typename T>
 hipError_t launch_persistent(const PersistArgs& P, int grid, int block, hipStream_t s);
 template <typename T>
-hipError_t launch_rollout_fwd(const AdjArgs& A, const ClassT<T>& C, int m, bool shaped, hipStream_t s);
+hipError_t launch_rollout_fwd(const AdjArgs& A, const ClassT<T>& C, int m, bool shaped, int n_cu, hipStream_t s);
 template <typename T>
 hipError_t launch_rollout_bwd(const AdjArgs& A, const ClassT<T>& C, int m, bool shaped, hipStream_t s);
 

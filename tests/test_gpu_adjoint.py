@@ -213,10 +213,12 @@ def test_classes_in_one_batch_match_each_class_alone():
 
 @pytest.mark.parametrize("H_,hold,ckpt,n,precision", [
     (1, 1, 32, 64, mgx.FP32), (3, 1, 1, 70, mgx.FP32), (5, 8, 4, 64, mgx.FP32), (33, 1, 32, 130, mgx.FP32),
-    (64, 3, 32, 64, mgx.FP32), (67, 5, 7, 70, mgx.FP64)])
+    (64, 3, 32, 64, mgx.FP32), (67, 5, 7, 70, mgx.FP64), (33, 1, 32, 22000, mgx.FP32), (5, 8, 4, 22000, mgx.FP32),
+    (3, 1, 1, 22000, mgx.FP64)])
 def test_forward_rows_ahead_at_their_edges(H_, hold, ckpt, n, precision):
     """The forward pass keeps four action rows in flight: horizons below, at and past
-    multiples of four, holds, and checkpoints at every phase. Positions are those of single
+    multiples of four, holds, and checkpoints at every phase, for few tiles (three waves each)
+    and many (two). Positions are those of single
     steps and gradients those of one segment, bit for bit (the same operations in the same
     order, so no tolerance)."""
     t = torch()
