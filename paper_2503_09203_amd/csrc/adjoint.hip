@@ -115,12 +115,34 @@ __device__ __forceinline__ void load_action(const AdjArgs& A, int64_t row, int64
     for (int i = 0; i < M; ++i) raw[i] = src[i * (int64_t)A.npad];
 }
 
-// Row k of segment `seg` in a tile's block of the recompute buffer (states) and of the tape,
+// Fields of a recompute row: q and nu. The reverse of a step reads neither the position nor
+// the rotor states before it, and a wave can have no more than 63 vector memory operations
+// outstanding: the recomputation's stores bound it (57 a step with 8 thrusters, now 46; the
+// two-wave backward of 65,536 x 64 312 -> 268 us, the forward 149 -> 127).
+constexpr int kSegFields = 10;
+
+template <typename T>
+__device__ __forceinline__ void store_seg(T* row, int lane, const RigidT<T>& s) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) row[j * kWave + lane] = s.q[j];
+#pragma unroll
+    for (int j = 0; j < 6; ++j) row[(4 + j) * kWave + lane] = s.nu[j];
+}
+
+template <typename T>
+__device__ __forceinline__ void load_seg(const T* row, int lane, RigidT<T>& s) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s.q[j] = row[j * kWave + lane];
+#pragma unroll
+    for (int j = 0; j < 6; ++j) s.nu[j] = row[(4 + j) * kWave + lane];
+}
+
+// Row k of segment `seg` in a tile's block of the recompute buffer and of the tape,
 // both [tile][2 x ckpt rows][field][64 lanes]; consecutive segments alternate between the
 // two halves of a block.
-template <typename T, int M>
+template <typename T>
 __device__ __forceinline__ T* seg_row_of(const AdjArgs& A, int64_t tile, int seg, int k) {
-    constexpr int kRow = (kStateFixed + M) * kWave;
+    constexpr int kRow = kSegFields * kWave;
     return (T*)A.seg_buf + (tile * 2 * A.ckpt + (seg & 1) * A.ckpt + (k - seg * A.ckpt)) * kRow;
 }
 template <typename T>
@@ -130,7 +152,7 @@ __device__ __forceinline__ T* tape_row_of(const AdjArgs& A, int64_t tile, int se
 }
 
 // Segment `seg` (steps k0 .. k1 - 1) run from its checkpoint the way the reverse sweep needs
-// it: each step's state before the step into the recompute buffer, and its forward
+// it: each step's attitude and velocity before it into the recompute buffer, and its forward
 // quantities and the actions' clip mask into the tape. Used by the forward pass for the last
 // segment and by the backward for the others; the actions of step k + 1 are in flight while
 // step k runs. `after(k)` is called at the end of step k.
@@ -160,7 +182,7 @@ __device__ __forceinline__ void recompute_segment(const AdjArgs& A, const ClassT
     for (int k = k0; k < k1; ++k) {
         load_action<T, M>(A, k + 1 < k1 ? rc.next_row() : rc.row, e, nxt);
         rc.advance();
-        store_state<T, M>(seg_row_of<T, M>(A, tile, seg, k), kWave, lane, s);
+        store_seg<T>(seg_row_of<T>(A, tile, seg, k), lane, s);
         VjpTape<T> tp;
         step_body<T, M, false, kShaped, false, false, false, true>(C, E, IA2, Brb, s, a, nullptr, nullptr, &tp);
         T* tr = tape_row_of<T>(A, tile, seg, k);
@@ -374,6 +396,21 @@ __global__ void __launch_bounds__(3 * kWave) k_rollout_fwd_ahead(AdjArgs A, Clas
     store_rigid<T>((T*)A.state, np, e, s);
 }
 
+// The parameter adjoints of environment e.
+template <typename T>
+__device__ __forceinline__ void store_dparams(const AdjArgs& A, const ClassT<T>& C, const EnvT<T>& E, int64_t e,
+                                              const T gdL[6], const T gdQ[6], const T gA[6], const T gDt[6]) {
+    T* gp = (T*)A.dparams + e;
+    const int64_t np = A.npad;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+        gp[j * np] = gdL[j];
+        gp[(6 + j) * np] = gdQ[j];
+        // dt M^-1 = dt / (M_RB + M_A): d/dM_A = -(dt M^-1)^2 / dt
+        gp[(12 + j) * np] = gA[j] - gDt[j] * E.dtMinv[j] * E.dtMinv[j] * C.inv_dt;
+    }
+}
+
 // Reverse sweep with per-segment recomputation. Two waves per 64-environment tile (block of
 // 128): wave 1 recomputes segment s - 1 from its checkpoint into one half of the segment
 // buffer while wave 0 sweeps segment s backwards from the other half, so recomputation
@@ -398,7 +435,7 @@ __global__ void __launch_bounds__(128) k_rollout_bwd(AdjArgs A, ClassT<T> Cs) {
     // this tile's blocks of the recompute buffer and the tape (the layout of seg_row_of and
     // tape_row_of, with the tile's base hoisted); within a row, field f of lane l at
     // f * kWave + l
-    constexpr int kSegRow = (kStateFixed + M) * kWave, kTapeRow = kTapeFields * kWave;
+    constexpr int kSegRow = kSegFields * kWave, kTapeRow = kTapeFields * kWave;
     const int lane = threadIdx.x & (kWave - 1);
     T* sg = (T*)A.seg_buf + (int64_t)blockIdx.x * 2 * A.ckpt * kSegRow;
     T* tb = (T*)A.tape_buf + (int64_t)blockIdx.x * 2 * A.ckpt * kTapeRow;
@@ -448,7 +485,7 @@ __global__ void __launch_bounds__(128) k_rollout_bwd(AdjArgs A, ClassT<T> Cs) {
         };
         Buf b0, b1;
         auto fetch = [&](Buf& b, int k) {
-            load_state<T, M>(seg_row(seg, k), kWave, lane, b.s);
+            load_seg<T>(seg_row(seg, k), lane, b.s);
             const T* tr = tape_row(seg, k);
             load_tape<T, M>(tr, kWave, lane, b.tp);
             b.pass = tr[kTapeLen * kWave + lane];
@@ -491,15 +528,169 @@ __global__ void __launch_bounds__(128) k_rollout_bwd(AdjArgs A, ClassT<T> Cs) {
 #pragma unroll
         for (int i = 0; i < M; ++i) dact[row_cur * A.row_stride + i * np + e] = arow[i];
     }
-    if (A.dparams) {
-        T* gp = (T*)A.dparams;
-        const T inv_dt = C.inv_dt;
+    if (A.dparams) store_dparams<T>(A, C, E, e, gdL, gdQ, gA, gDt);
+}
+
+// The reverse sweep in three waves per tile (block of 192), for launches of few tiles: wave 0
+// sweeps pose and velocity, wave 1 recomputes the segment before, and wave 2 takes what the
+// sweep does not wait for (rotor states, commands, parameter adjoints), from the adjoint of
+// each step's velocity update handed over in LDS. With a SIMD for each wave the sweep's own
+// instructions bound the launch (520 a step with 8 thrusters, 390 without that half): 8192 x
+// 256 318 -> 275 us, in double 1105 -> 529 (the two-wave form spills there). With the recompute
+// rows cut to what the reverse reads: 255 and 453.
+// Steps go in groups of kBwdGroup, each ended by a barrier of all three waves: wave 2 works on
+// a group while the sweep runs the next into the other buffer. It fetches its part of the
+// group's rows before that barrier, since after the one that ends a segment wave 1 writes over
+// them. Wave 1 ends a segment's groups only once its own segment is whole.
+template <typename T>
+constexpr int kBwdGroup = sizeof(T) == 4 ? 4 : 2;  // even: the sweep's buffers alternate
+
+template <typename T, int M, bool kShaped>
+__global__ void __launch_bounds__(3 * kWave) k_rollout_bwd_split(AdjArgs A, ClassT<T> Cs) {
+    constexpr int G = kBwdGroup<T>;
+    __shared__ T ring[2][G][6][kWave];
+    const int role = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t tile = blockIdx.x, e = tile * kWave + lane, np = A.npad;
+    const ClassT<T> C = class_in_vgpr<T, M>(Cs);
+    EnvT<T> E;
+    load_env<T>((const T*)A.rec, np, e, E);
+    set_amc(E, C.flags);
+    const int nseg = (A.H + A.ckpt - 1) / A.ckpt;
+    auto seg_end = [&](int seg) { return (seg + 1) * (int64_t)A.ckpt < A.H ? (seg + 1) * A.ckpt : A.H; };
+
+    if (role == 2) {
+        T* dact = (T*)A.dactions;
+        T nb[M], arow[M];
 #pragma unroll
-        for (int j = 0; j < 6; ++j) {
-            gp[j * np + e] = gdL[j];
-            gp[(6 + j) * np + e] = gdQ[j];
-            // dt M^-1 = dt / (M_RB + M_A): d/dM_A = -(dt M^-1)^2 / dt
-            gp[(12 + j) * np + e] = gA[j] - gDt[j] * E.dtMinv[j] * E.dtMinv[j] * inv_dt;
+        for (int i = 0; i < M; ++i) nb[i] = arow[i] = T(0);
+        T gdL[6], gdQ[6], gA[6], gDt[6];
+#pragma unroll
+        for (int j = 0; j < 6; ++j) gdL[j] = gdQ[j] = gA[j] = gDt[j] = T(0);
+        RowCursor rb(A, A.t0 + A.H - 1);
+        int64_t row_cur = -1;
+        auto store_row = [&]() {
+            if (row_cur >= 0 && dact) {
+#pragma unroll
+                for (int i = 0; i < M; ++i) dact[row_cur * A.row_stride + i * np + e] = arow[i];
+            }
+        };
+        struct Row {
+            T fd[M], nu[6], vc[3], F[6], pass;
+        };
+        Row row[G];
+        for (int seg = nseg - 1, buf = 0; seg >= 0; --seg) {
+            const int k0 = seg * A.ckpt;
+            for (int k1 = seg_end(seg) - 1; k1 >= k0; k1 -= G, buf ^= 1) {
+#pragma unroll
+                for (int u = 0; u < G; ++u) {
+                    const int k = k1 - u > k0 ? k1 - u : k0;  // a group cut short repeats its last row
+                    const T* sr = seg_row_of<T>(A, tile, seg, k) + lane;
+                    const T* tr = tape_row_of<T>(A, tile, seg, k) + lane;
+                    Row& r = row[u];
+#pragma unroll
+                    for (int i = 0; i < M; ++i) r.fd[i] = tr[i * kWave];
+#pragma unroll
+                    for (int j = 0; j < 6; ++j) r.nu[j] = sr[(4 + j) * kWave];
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) r.vc[j] = tr[(kMaxThr + 9 + j) * kWave];
+#pragma unroll
+                    for (int j = 0; j < 6; ++j) r.F[j] = tr[(kMaxThr + 12 + j) * kWave];
+                    r.pass = tr[kTapeLen * kWave];
+                }
+                __builtin_amdgcn_s_waitcnt(0);  // the rows are here before the barrier frees them
+                __syncthreads();
+#pragma unroll
+                for (int u = 0; u < G; ++u) {
+                    if (k1 - u < k0) break;
+                    T nu1b[6], ab[M];
+#pragma unroll
+                    for (int j = 0; j < 6; ++j) nu1b[j] = ring[buf][u][j][lane];
+                    VjpShared<T> h2;
+                    vjp_shared<T>(E, row[u].nu, row[u].vc, nu1b, h2);
+                    vjp_params<T, M>(C, row[u].nu, row[u].vc, row[u].F, row[u].fd, nu1b, h2, nb, ab, gdL, gdQ, gA,
+                                     gDt);
+                    if (rb.row != row_cur) {
+                        store_row();
+                        row_cur = rb.row;
+#pragma unroll
+                        for (int i = 0; i < M; ++i) arow[i] = T(0);
+                    }
+                    rb.retreat();
+                    const uint32_t pass = (uint32_t)row[u].pass;
+#pragma unroll
+                    for (int i = 0; i < M; ++i) arow[i] += ((pass >> i) & 1u) ? ab[i] : T(0);
+                }
+            }
+        }
+        store_row();
+        if (A.dparams) store_dparams<T>(A, C, E, e, gdL, gdQ, gA, gDt);
+        return;
+    }
+
+    T IA2[3], Brb[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        IA2[j] = C.inertia[j] + E.A[3 + j];
+        Brb[j] = E.buoy * C.rb[j];
+    }
+    if (role == 1) {
+        for (int seg = nseg - 1; seg >= 0; --seg) {
+            int left = (seg_end(seg) - seg * A.ckpt - 1) / G, n = 0;  // barriers before the segment's last
+            if (seg > 0)
+                recompute_segment<T, M, kShaped>(A, C, E, IA2, Brb, e, lane, seg - 1, [&](int) {
+                    if (++n % G == 0 && left > 0) {
+                        __syncthreads();
+                        --left;
+                    }
+                });
+            for (; left >= 0; --left) __syncthreads();
+        }
+        return;
+    }
+
+    const T* dpos = (const T*)A.pos + e;
+    RigidT<T> xb;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) xb.p[j] = T(0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) xb.q[j] = T(0);
+#pragma unroll
+    for (int j = 0; j < 6; ++j) xb.nu[j] = T(0);
+    for (int seg = nseg - 1, buf = 0; seg >= 0; --seg) {
+        const int k0 = seg * A.ckpt;
+        // row k - 1 is fetched while step k runs, into the other of two buffers
+        struct Buf {
+            RigidT<T> s;
+            VjpTape<T> tp;  // its thrust slopes are wave 2's
+            T dp[3];
+        };
+        Buf b0, b1;
+        auto fetch = [&](Buf& b, int k) {
+            load_seg<T>(seg_row_of<T>(A, tile, seg, k), lane, b.s);
+            load_tape<T, 0>(tape_row_of<T>(A, tile, seg, k), kWave, lane, b.tp);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) b.dp[j] = dpos[(int64_t)k * A.pos_stride + j * np];
+        };
+        auto reverse_step = [&](Buf& cur, Buf& nxt, int k, T out[6][kWave]) {
+            T nu1b[6];
+#pragma unroll
+            for (int j = 0; j < 3; ++j) xb.p[j] += cur.dp[j];
+            fetch(nxt, k > k0 ? k - 1 : k0);
+            VjpShared<T> h2;  // for the other half, which forms it by itself
+            vjp_rigid<T>(C, E, IA2, Brb, cur.s, cur.tp, xb, nu1b, h2);
+#pragma unroll
+            for (int j = 0; j < 6; ++j) out[j][lane] = nu1b[j];
+        };
+        int k = seg_end(seg) - 1;
+        fetch(b0, k);
+        for (; k >= k0; buf ^= 1) {
+#pragma unroll
+            for (int u = 0; u < G; u += 2) {
+                if (k >= k0) reverse_step(b0, b1, k--, ring[buf][u]);
+                if (k >= k0) reverse_step(b1, b0, k--, ring[buf][u + 1]);
+            }
+            __syncthreads();
         }
     }
 }
@@ -528,8 +719,9 @@ __global__ void __launch_bounds__(128) k_rollout_bwd(AdjArgs A, ClassT<T> Cs) {
 
 // Whether the three waves of every tile find a SIMD each. Up to there the three-wave forms are
 // faster (forward pass of 16,384 x 128 90 against 105 us, in double 89 against 98 for
-// 16,384 x 64); beyond, the SIMDs fill with whole tiles and the hand-over only adds work
-// (65,536 x 64: 168 against 149; in double 169 against 145 for 32,768 x 64).
+// 16,384 x 64; backward of 8192 x 256 275 against 318); beyond, the SIMDs fill with whole tiles
+// and the hand-over only adds work (forward of 65,536 x 64 168 against 149; in double 169
+// against 145 for 32,768 x 64).
 static bool wave_per_simd(int64_t npad, int n_cu) { return 3 * (npad / kWave) <= 4 * (int64_t)n_cu; }
 
 template <typename T>
@@ -555,20 +747,27 @@ hipError_t launch_rollout_fwd(const AdjArgs& A, const ClassT<T>& C, int m, bool 
 }
 
 template <typename T>
-hipError_t launch_rollout_bwd(const AdjArgs& A, const ClassT<T>& C, int m, bool shaped, hipStream_t s) {
-    // one block of two waves per 64-environment tile; npad is a multiple of 64
+hipError_t launch_rollout_bwd(const AdjArgs& A, const ClassT<T>& C, int m, bool shaped, int n_cu, hipStream_t s) {
     if (A.npad % kWave != 0) return hipErrorInvalidValue;
-    const unsigned grid = (unsigned)(A.npad / kWave), block = 2 * kWave;
-#define KERNEL k_rollout_bwd
-    MGX_ADJ_SWITCH
+    const unsigned grid = (unsigned)(A.npad / kWave);
+    if (wave_per_simd(A.npad, n_cu)) {
+        const unsigned block = 3 * kWave;
+#define KERNEL k_rollout_bwd_split
+        MGX_ADJ_SWITCH
 #undef KERNEL
+    } else {
+        const unsigned block = 2 * kWave;
+#define KERNEL k_rollout_bwd
+        MGX_ADJ_SWITCH
+#undef KERNEL
+    }
     return hipGetLastError();
 }
 
 template hipError_t launch_rollout_fwd<float>(const AdjArgs&, const ClassT<float>&, int, bool, int, hipStream_t);
 template hipError_t launch_rollout_fwd<double>(const AdjArgs&, const ClassT<double>&, int, bool, int, hipStream_t);
-template hipError_t launch_rollout_bwd<float>(const AdjArgs&, const ClassT<float>&, int, bool, hipStream_t);
-template hipError_t launch_rollout_bwd<double>(const AdjArgs&, const ClassT<double>&, int, bool, hipStream_t);
+template hipError_t launch_rollout_bwd<float>(const AdjArgs&, const ClassT<float>&, int, bool, int, hipStream_t);
+template hipError_t launch_rollout_bwd<double>(const AdjArgs&, const ClassT<double>&, int, bool, int, hipStream_t);
 
 }  // namespace mgx
 
@@ -761,9 +960,9 @@ extern "C" mgx_status mgx_rollout_backward(mgx_batch* b, const void* dpos, void*
         A.dparams = dparams ? (char*)dparams + P * 18 * b->pad_off[c] : nullptr;
         hipError_t e;
         if (b->prec == MGX_FP32)
-            e = launch_rollout_bwd<float>(A, b->h_class_f[c], b->m[c], class_shaped(b, c), b->stream);
+            e = launch_rollout_bwd<float>(A, b->h_class_f[c], b->m[c], class_shaped(b, c), b->n_cu, b->stream);
         else
-            e = launch_rollout_bwd<double>(A, b->h_class_d[c], b->m[c], class_shaped(b, c), b->stream);
+            e = launch_rollout_bwd<double>(A, b->h_class_d[c], b->m[c], class_shaped(b, c), b->n_cu, b->stream);
         if (e != hipSuccess) return hip_fail(b, e, "rollout backward launch");
     }
     return MGX_OK;

@@ -140,15 +140,21 @@ __host__ __device__ __forceinline__ void vjp_forward(const ClassT<T>& C, const E
     }
 }
 
-// Reverse part: given the state before the step, its tape and the adjoint of the state
-// after the step, the adjoint of the state before it and of the commands, accumulating the
-// parameter adjoints. The cheap forward quantities are formed again from the state and the
-// tape.
-template <typename T, int M, bool kShaped = false>
-__host__ __device__ __forceinline__ void vjp_reverse(const ClassT<T>& C, const EnvT<T>& E, const T IA2[3],
-                                                     const T Brb[3], const StateT<T, M>& s, const VjpTape<T>& tp,
-                                                     StateT<T, M>& xb, T abar[M], T gdL[6], T gdQ[6], T gA[6],
-                                                     T gDt[6]) {
+// What both halves of the reverse part use: the relative velocity, the adjoints of the total
+// force, of A_1 v_r and of (I + A_2) w.
+template <typename T>
+struct VjpShared {
+    T vr[3], Fb[6], A1vrb[3], Lb[3];
+};
+
+// Rigid-body half of the reverse part: from the state before the step (without its rotors), its
+// tape and the adjoint of the state after the step, the adjoint of the state before it, and
+// nu1b, the adjoint of the step's velocity update, which is all that the other half needs. The
+// cheap forward quantities are formed again from the state and the tape.
+template <typename T>
+__host__ __device__ __forceinline__ void vjp_rigid(const ClassT<T>& C, const EnvT<T>& E, const T IA2[3],
+                                                   const T Brb[3], const RigidT<T>& s, const VjpTape<T>& tp,
+                                                   RigidT<T>& xb, T nu1b[6], VjpShared<T>& h2) {
 #pragma clang fp contract(fast)
     const T qw = s.q[0], qx = s.q[1], qy = s.q[2], qz = s.q[3];
     const T R[3][3] = {{tp.R[0], tp.R[1], tp.R[2]}, {tp.R[3], tp.R[4], tp.R[5]}, {tp.R[6], tp.R[7], tp.R[8]}};
@@ -165,8 +171,6 @@ __host__ __device__ __forceinline__ void vjp_reverse(const ClassT<T>& C, const E
         L[j] = IA2[j] * w[j];
     }
     const bool amc = !(C.flags & kFlagNoAmc);
-    T wvc[3] = {T(0), T(0), T(0)};
-    if (amc) cross(w, vc, wvc);
     T nu1[6];
 #pragma unroll
     for (int j = 0; j < 6; ++j) nu1[j] = s.nu[j] + E.dtMinv[j] * F[j];
@@ -202,7 +206,6 @@ __host__ __device__ __forceinline__ void vjp_reverse(const ClassT<T>& C, const E
     // d = (c, sh w1), c and sh functions of phi2 = h^2 |w1|^2
     const T shb = db[1] * w1[0] + db[2] * w1[1] + db[3] * w1[2];
     const T phi2b = db[0] * dc + shb * dsh;
-    T nu1b[6];
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
         nu1b[j] = xb.nu[j];
@@ -221,18 +224,11 @@ __host__ __device__ __forceinline__ void vjp_reverse(const ClassT<T>& C, const E
     // nu+ = nu + dtMinv F
     T Fb[6];
 #pragma unroll
-    for (int j = 0; j < 6; ++j) {
-        Fb[j] = E.dtMinv[j] * nu1b[j];
-        gDt[j] += F[j] * nu1b[j];
-    }
-    T taub[6], gbb[3], vb[3] = {T(0), T(0), T(0)}, wb[3] = {T(0), T(0), T(0)}, vrb[3] = {T(0), T(0), T(0)},
-                       vcb[3] = {T(0), T(0), T(0)};
+    for (int j = 0; j < 6; ++j) Fb[j] = E.dtMinv[j] * nu1b[j];
+    T gbb[3], vb[3] = {T(0), T(0), T(0)}, wb[3] = {T(0), T(0), T(0)}, vrb[3] = {T(0), T(0), T(0)},
+              vcb[3] = {T(0), T(0), T(0)};
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
-        taub[j] = Fb[j];
-        taub[3 + j] = Fb[3 + j];
-        gbb[j] = E.wmb * Fb[j];
-    }
+    for (int j = 0; j < 3; ++j) gbb[j] = E.wmb * Fb[j];
     // restoring moment rmom = Brb x gb, F_ang -= rmom
     {
         const T rmomb[3] = {-Fb[3], -Fb[4], -Fb[5]};
@@ -246,20 +242,13 @@ __host__ __device__ __forceinline__ void vjp_reverse(const ClassT<T>& C, const E
     for (int j = 0; j < 3; ++j) {
         const T bl = -Fb[j], ba = -Fb[3 + j];
         vrb[j] += bl * fma_(T(2) * E.dQ[j], abs_(vr[j]), E.dL[j]);
-        gdL[j] += bl * vr[j];
-        gdQ[j] += bl * abs_(vr[j]) * vr[j];
         wb[j] += ba * fma_(T(2) * E.dQ[3 + j], abs_(w[j]), E.dL[3 + j]);
-        gdL[3 + j] += ba * w[j];
-        gdQ[3 + j] += ba * abs_(w[j]) * w[j];
     }
     // current term hA = A1 (w x vc), F_lin -= hA
     if (amc) {
         T ub[3];
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            gA[j] += -Fb[j] * wvc[j];
-            ub[j] = E.A[j] * -Fb[j];
-        }
+        for (int j = 0; j < 3; ++j) ub[j] = E.A[j] * -Fb[j];
         cross_bar(w, vc, ub, wb, vcb);
     }
     // Coriolis, linear rows: cor_lin = w x P, F_lin -= cor_lin
@@ -279,12 +268,10 @@ __host__ __device__ __forceinline__ void vjp_reverse(const ClassT<T>& C, const E
     for (int j = 0; j < 3; ++j) {
         // L = (I + A2) w
         wb[j] += IA2[j] * Lb[j];
-        gA[3 + j] += w[j] * Lb[j];
         // P = m v + A1vr
         vb[j] += E.mass * Pb[j];
         A1vrb[j] += Pb[j];
         // A1vr = A1 vr
-        gA[j] += vr[j] * A1vrb[j];
         vrb[j] += E.A[j] * A1vrb[j];
         // vr = v - vc
         vb[j] += vrb[j];
@@ -305,15 +292,13 @@ __host__ __device__ __forceinline__ void vjp_reverse(const ClassT<T>& C, const E
              T(4) * qy * (Rb[0][0] + Rb[2][2]);
     qb[3] += T(2) * (-qw * Rb[0][1] + qx * Rb[0][2] + qw * Rb[1][0] + qy * Rb[1][2] + qx * Rb[2][0] + qy * Rb[2][1]) -
              T(4) * qz * (Rb[0][0] + Rb[1][1]);
-    // thrust and lag
 #pragma unroll
-    for (int i = 0; i < M; ++i) {
-        T fb = T(0);
-#pragma unroll
-        for (int j = 0; j < 6; ++j) fb = fma_(C.Bk[j][i], taub[j], fb);
-        const T nlb = fb * tp.fd[i] + xb.n[i];
-        abar[i] = C.alpha[i] * nlb;
-        xb.n[i] = (T(1) - C.alpha[i]) * nlb;
+    for (int j = 0; j < 3; ++j) {
+        h2.vr[j] = vr[j];
+        h2.Fb[j] = Fb[j];
+        h2.Fb[3 + j] = Fb[3 + j];
+        h2.A1vrb[j] = A1vrb[j];
+        h2.Lb[j] = Lb[j];
     }
     // write the adjoint of the state before the step (p passes through)
 #pragma unroll
@@ -325,6 +310,83 @@ __host__ __device__ __forceinline__ void vjp_reverse(const ClassT<T>& C, const E
     }
 }
 
+// The shared quantities from nu1b alone (nu and vc: the step's velocity and current, body
+// frame), where the other half runs by itself.
+template <typename T>
+__host__ __device__ __forceinline__ void vjp_shared(const EnvT<T>& E, const T nu[6], const T vc[3], const T nu1b[6],
+                                                    VjpShared<T>& h2) {
+#pragma clang fp contract(fast)
+    const T* w = nu + 3;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) h2.vr[j] = nu[j] - vc[j];
+#pragma unroll
+    for (int j = 0; j < 6; ++j) h2.Fb[j] = E.dtMinv[j] * nu1b[j];
+    const T* Fb = h2.Fb;
+    const T cl[3] = {-Fb[0], -Fb[1], -Fb[2]}, ca[3] = {-Fb[3], -Fb[4], -Fb[5]};
+    T Pb[3];
+    cross(cl, w, Pb);
+    cross(ca, w, h2.Lb);
+    cross(ca, h2.vr, h2.A1vrb);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) h2.A1vrb[j] += Pb[j];
+}
+
+// The half that nothing of the sweep waits for: the adjoint of the commands, of the rotor
+// states (nb: after the step, then before it) and the parameter adjoints' sums. F is the step's
+// total force, fd its thrust slopes.
+template <typename T, int M>
+__host__ __device__ __forceinline__ void vjp_params(const ClassT<T>& C, const T nu[6], const T vc[3], const T F[6],
+                                                    const T* fd, const T nu1b[6], const VjpShared<T>& h2, T nb[M],
+                                                    T abar[M], T gdL[6], T gdQ[6], T gA[6], T gDt[6]) {
+#pragma clang fp contract(fast)
+    const T *w = nu + 3, *vr = h2.vr, *Fb = h2.Fb;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) gDt[j] += F[j] * nu1b[j];
+    // damping
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const T bl = -Fb[j], ba = -Fb[3 + j];
+        gdL[j] += bl * vr[j];
+        gdQ[j] += bl * abs_(vr[j]) * vr[j];
+        gdL[3 + j] += ba * w[j];
+        gdQ[3 + j] += ba * abs_(w[j]) * w[j];
+    }
+    // added mass: the current term A1 (w x vc), then P, L and A1vr of the Coriolis rows
+    if (!(C.flags & kFlagNoAmc)) {
+        T wvc[3];
+        cross(w, vc, wvc);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) gA[j] += -Fb[j] * wvc[j];
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        gA[3 + j] += w[j] * h2.Lb[j];
+        gA[j] += vr[j] * h2.A1vrb[j];
+    }
+    // thrust and lag
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+        T fb = T(0);
+#pragma unroll
+        for (int j = 0; j < 6; ++j) fb = fma_(C.Bk[j][i], Fb[j], fb);
+        const T nlb = fb * fd[i] + nb[i];
+        abar[i] = C.alpha[i] * nlb;
+        nb[i] = (T(1) - C.alpha[i]) * nlb;
+    }
+}
+
+// The reverse part: the adjoint of the state before the step and of the commands, accumulating
+// the parameter adjoints.
+template <typename T, int M, bool kShaped = false>
+__host__ __device__ __forceinline__ void vjp_reverse(const ClassT<T>& C, const EnvT<T>& E, const T IA2[3],
+                                                     const T Brb[3], const StateT<T, M>& s, const VjpTape<T>& tp,
+                                                     StateT<T, M>& xb, T abar[M], T gdL[6], T gdQ[6], T gA[6],
+                                                     T gDt[6]) {
+    T nu1b[6];
+    VjpShared<T> h2;
+    vjp_rigid<T>(C, E, IA2, Brb, s, tp, xb, nu1b, h2);
+    vjp_params<T, M>(C, s.nu, tp.vc, tp.F, tp.fd, nu1b, h2, xb.n, abar, gdL, gdQ, gA, gDt);
+}
 
 // The vector-Jacobian product of one step (written out by hand in reverse order of the
 // forward pass): its forward part, then its reverse part.

@@ -333,6 +333,6 @@ hipError_t launch_persistent(const PersistArgs& P, int grid, int block, hipStrea
 template <typename T>
 hipError_t launch_rollout_fwd(const AdjArgs& A, const ClassT<T>& C, int m, bool shaped, int n_cu, hipStream_t s);
 template <typename T>
-hipError_t launch_rollout_bwd(const AdjArgs& A, const ClassT<T>& C, int m, bool shaped, hipStream_t s);
+hipError_t launch_rollout_bwd(const AdjArgs& A, const ClassT<T>& C, int m, bool shaped, int n_cu, hipStream_t s);
 
 }  // namespace mgx
