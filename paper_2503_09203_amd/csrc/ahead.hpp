@@ -47,7 +47,7 @@ __device__ __forceinline__ int ahead_group_end(int k0, int group, int seg, int K
 // The thrust wave: rotor states, command rows and their bookkeeping as in env_steps.
 template <typename T, int M, bool kOut, bool kShaped, bool kFins, bool kSeg>
 __device__ __forceinline__ void ahead_thrust(const StepArgs& A, const ClassT<T>& Cs, int64_t env, int lane, bool live,
-                                             int64_t t0, AheadRing<T, M, kFins>& ring) {
+                                             int64_t t0, int seg, AheadRing<T, M, kFins>& ring) {
     const int group = ring.group(A.K);
     const int64_t np = A.npad;
     T* S = (T*)A.state + kStateFixed * np + env;
@@ -55,7 +55,7 @@ __device__ __forceinline__ void ahead_thrust(const StepArgs& A, const ClassT<T>&
 #pragma unroll
     for (int i = 0; i < M; ++i) n[i] = S[i * np];
     const ClassT<T> C = class_in_vgpr<T, M, false, kFins>(Cs);
-    const int K = A.K, seg = A.seg;
+    const int K = A.K;
     const int64_t hold = A.hold, nrows = A.n_rows, rstride = A.row_stride;
     const T* abase = (const T*)A.actions + env;
     auto clamp_row = [nrows](int64_t x) { return x < 0 ? (int64_t)0 : (x >= nrows ? nrows - 1 : x); };
@@ -115,7 +115,7 @@ __device__ __forceinline__ void ahead_thrust(const StepArgs& A, const ClassT<T>&
 // The rigid-body wave.
 template <typename T, int M, bool kOut, bool kFins, bool kPayload, bool kSeg>
 __device__ __forceinline__ void ahead_rigid(const StepArgs& A, const ClassT<T>& Cs, int64_t env, int lane, bool live,
-                                            const AheadRing<T, M, kFins>& ring) {
+                                            int seg, const AheadRing<T, M, kFins>& ring) {
     const int group = ring.group(A.K);
     const int64_t np = A.npad;
     MGX_WAVE_TS(ts_entry);
@@ -134,7 +134,7 @@ __device__ __forceinline__ void ahead_rigid(const StepArgs& A, const ClassT<T>& 
     env_prologue<T, kPayload>(C, E, IA2, Brb);
     __builtin_amdgcn_s_waitcnt(0);
     MGX_WAVE_TS(ts_loaded);
-    const int K = A.K, seg = A.seg;
+    const int K = A.K;
     [[clang::code_align(64)]] for (int k0 = 0, buf = 0, end = seg; k0 < K; buf ^= 1) {
         const int k1 = kSeg ? ahead_group_end(k0, group, seg, K, end) : k0 + group < K ? k0 + group : K;
         __syncthreads();
@@ -185,7 +185,7 @@ __device__ __forceinline__ void ahead_rigid(const StepArgs& A, const ClassT<T>& 
 // Blocks of up to kAheadTiles tiles: the first half of a block's waves are the rigid-body
 // waves, so that with four tiles each SIMD of the compute unit holds one wave of either
 // kind. Waves past the segment run its last tile and store nothing.
-// kSeg: the launch holds several stretches of A.seg steps (a kernel of its own: the cut of
+// kSeg: the launch holds several stretches of L.seg steps (a kernel of its own: the cut of
 // the hand-over groups at the stretches' ends costs a double launch of one stretch 10%).
 template <typename T, int M, bool kOut, bool kShaped, bool kFins, bool kPayload, bool kSeg>
 __global__ void __launch_bounds__(2 * kAheadTiles * kWave) k_step_ahead(StepLaunch<T> L) {
@@ -203,9 +203,9 @@ __global__ void __launch_bounds__(2 * kAheadTiles * kWave) k_step_ahead(StepLaun
         prepare_next_slot(A.misc, A.wr);
     }
     if (wv >= tiles)
-        ahead_thrust<T, M, kOut, kShaped, kFins, kSeg>(A, L.cls, env, lane, live, t0, rings[slot]);
+        ahead_thrust<T, M, kOut, kShaped, kFins, kSeg>(A, L.cls, env, lane, live, t0, L.seg, rings[slot]);
     else
-        ahead_rigid<T, M, kOut, kFins, kPayload, kSeg>(A, L.cls, env, lane, live, rings[slot]);
+        ahead_rigid<T, M, kOut, kFins, kPayload, kSeg>(A, L.cls, env, lane, live, L.seg, rings[slot]);
 }
 
 }  // namespace mgx

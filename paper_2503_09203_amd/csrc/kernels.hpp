@@ -239,11 +239,6 @@ struct StepArgs {
     int64_t n_rows, row0;
     int32_t class_index;
     int32_t advance;      // 0, or K: block 0 writes t[wr] = t[rd] + K
-    // Steps between the checks of the attitude's drift; K (at the launch's end only) but in the
-    // two-wave form, where a captured chunk runs many stretches in one launch with the checks,
-    // and the results, of as many launches.
-    int32_t seg;
-    int32_t pad;
     void* traj;           // class segment base within step row 0, or null
     int64_t traj_stride;  // elements per step row
     void* forces;         // class segment base within step row 0, or null
@@ -268,6 +263,12 @@ template <typename T>
 struct StepLaunch {
     StepArgs a;
     ClassT<T> cls;
+    // Steps between the checks of the attitude's drift; K (at the launch's end only) but in the
+    // two-wave form, where a captured chunk runs many stretches in one launch with the checks,
+    // and the results, of as many launches. Last, so that the class keeps its place in the
+    // arguments: eight bytes further on, one-step launches of the larger classes take 5% longer
+    // (65,536 environments: with fins 5.37 -> 5.62 us, with a payload 4.32 -> 4.53).
+    int32_t seg;
 };
 
 // Differentiable rollout, one class segment.

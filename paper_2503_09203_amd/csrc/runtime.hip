@@ -647,7 +647,6 @@ mgx_status enqueue_step(mgx_batch* b, const void* actions, int64_t n_rows, int64
         a.misc = b->d_misc;
         a.class_index = c;
         a.advance = (c == b->n_classes - 1) ? K : 0;
-        a.seg = seg;
         a.rd = b->slot;
         a.wr = 1 - b->slot;
         // a hint whose row lies outside the buffer is dropped: the launch then finds (and
@@ -664,10 +663,10 @@ mgx_status enqueue_step(mgx_batch* b, const void* actions, int64_t n_rows, int64
         a.stats = b->d_stats + (int64_t)kStats * c;
         hipError_t e;
         if (b->prec == MGX_FP32) {
-            StepLaunch<float> L{a, b->h_class_f[c]};
+            StepLaunch<float> L{a, b->h_class_f[c], seg};
             e = launch_step<float>(L, b->m[c], block, b->n_cu, b->stream);
         } else {
-            StepLaunch<double> L{a, b->h_class_d[c]};
+            StepLaunch<double> L{a, b->h_class_d[c], seg};
             e = launch_step<double>(L, b->m[c], block, b->n_cu, b->stream);
         }
         if (e != hipSuccess) return hip_fail(b, e, "step launch");

@@ -78,7 +78,7 @@ static void launch_step_body(const StepLaunch<T>& L, unsigned grid, int block, b
             const dim3 g((unsigned)((tiles + per - 1) / per)), b(2 * per * kWave);
             if (out)
                 hipLaunchKernelGGL((k_step_ahead<T, M, true, kShaped, kFins, kPayload, false>), g, b, 0, s, L);
-            else if (L.a.seg < L.a.K)
+            else if (L.seg < L.a.K)
                 hipLaunchKernelGGL((k_step_ahead<T, M, false, kShaped, kFins, kPayload, true>), g, b, 0, s, L);
             else
                 hipLaunchKernelGGL((k_step_ahead<T, M, false, kShaped, kFins, kPayload, false>), g, b, 0, s, L);
