@@ -69,16 +69,24 @@ static void launch_step_body(const StepLaunch<T>& L, unsigned grid, int block, b
                              int n_cu, hipStream_t s) {
     constexpr bool kDoubleFins = kFins && std::is_same<T, double>::value;
     if constexpr (!kDoubleFins) {
-        if (!L.a.partials && two_waves(L.a.npad, L.a.K, kDoubleFins, n_cu)) {
+        // Launches with outputs: both waves store, and those of the short hand-over groups only
+        // wait for each other (4,571 environments with the trajectory: 8 steps 8.4 -> 9.3 us,
+        // 64 steps 42.6 -> 45.1), so they take two waves only for longer launches of the
+        // float bodies with more to do per step (shaped 48.9 -> 45.6, payload 77 -> 71 for 64
+        // steps; at 32 and fewer shaped 26.6 -> 27.4).
+        constexpr bool kAheadOut = kShaped && !kFins && sizeof(T) == 4;
+        if (!L.a.partials && two_waves(L.a.npad, L.a.K, kDoubleFins, n_cu) &&
+            (!out || (kAheadOut && L.a.K > 32))) {
             // Four tiles to a block from two per compute unit on, so that every SIMD holds one
             // wave of either kind (a block's waves go round the SIMDs); fewer are spread over
             // more units.
             const int64_t tiles = L.a.npad / kWave;
             const int per = tiles > 2 * (int64_t)n_cu ? kAheadTiles : 1;
             const dim3 g((unsigned)((tiles + per - 1) / per)), b(2 * per * kWave);
-            if (out)
-                hipLaunchKernelGGL((k_step_ahead<T, M, true, kShaped, kFins, kPayload, false>), g, b, 0, s, L);
-            else if (L.seg < L.a.K)
+            if (out) {
+                if constexpr (kAheadOut)
+                    hipLaunchKernelGGL((k_step_ahead<T, M, true, kShaped, kFins, kPayload, false>), g, b, 0, s, L);
+            } else if (L.seg < L.a.K)
                 hipLaunchKernelGGL((k_step_ahead<T, M, false, kShaped, kFins, kPayload, true>), g, b, 0, s, L);
             else
                 hipLaunchKernelGGL((k_step_ahead<T, M, false, kShaped, kFins, kPayload, false>), g, b, 0, s, L);
