@@ -180,7 +180,21 @@ __device__ __forceinline__ void seeded_normals(uint64_t g, uint64_t seed, int j,
 template <typename T>
 __device__ __forceinline__ void seeded_state(uint64_t g, uint64_t seed, int m, T* state, int64_t npad, int64_t e) {
     double z[10];
-    for (int j = 0; j < 5; ++j) seeded_normals(g, seed, j, z[2 * j], z[2 * j + 1]);
+    // all words first, then the transforms: a lane drawing every pair itself (a session's
+    // initial state, a restart) runs the two loops one after the other
+    double u[10];
+    for (int j = 0; j < 5; ++j) {
+        uint32_t c[4] = {(uint32_t)g, 0u, (uint32_t)j, 0u};
+        philox4x32_10(c, (uint32_t)seed, kStreamInit << 24);
+        u[2 * j] = u53(c[0], c[1]);
+        u[2 * j + 1] = u53(c[2], c[3]);
+    }
+    for (int j = 0; j < 5; ++j) {
+        double rad = sqrt(-2.0 * log(1.0 - u[2 * j]));
+        double ang = 2.0 * M_PI * u[2 * j + 1];
+        z[2 * j] = rad * cos(ang);
+        z[2 * j + 1] = rad * sin(ang);
+    }
     double qn = sqrt(z[0] * z[0] + z[1] * z[1] + z[2] * z[2] + z[3] * z[3]);
     for (int j = 0; j < 3; ++j) state[j * npad + e] = (T)0;
     for (int j = 0; j < 4; ++j) state[(3 + j) * npad + e] = (T)(z[j] / qn);
