@@ -45,7 +45,7 @@ def bytes_per_env_step(m, K, hold, prec=4, rec_len=30):
 # of the step kernel comes from the committed rocprofv3 summary, and only while the kernel
 # sources still hash to the value recorded with those counters (else null).
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "k_step_dr65536x1000.md")
-KERNEL_SOURCES = ("step.hpp", "env_loop.hpp", "kernels.hip", "kernels.hpp", "step_kernel.hpp", "step_f32.hip")
+KERNEL_SOURCES = ("step.hpp", "env_loop.hpp", "kernels.hip", "kernels.hpp", "step_kernel.hpp", "ahead.hpp", "step_f32.hip")
 
 
 def kernel_sources_sha256(files=KERNEL_SOURCES):
@@ -282,13 +282,15 @@ def main():
     final_state = b.unpack_state(b.get_state().cpu().numpy().astype(np.float64))[0]
     value = N * T * args.steps / elapsed
 
-    # Fused kernel: HIP events on the batch's stream around every graph replay (the
-    # rollout's n_launch kernel launches back to back); average launch duration =
-    # elapsed / n_launch, so inter-kernel gaps count against the kernel.
+    # Fused kernel: HIP events on the batch's stream around every graph replay (the rollout's
+    # n_launch stretches of K steps). Up to a 64-environment tile per SIMD the graph joins up
+    # to 4096 steps of stretches in a launch; beyond, each stretch is a launch. The figures are
+    # per stretch = elapsed / n_launch, so gaps between launches count against the kernel.
     flops_es, ops_es = mgx.mgx_class_step_cost(mgx.mgx_class_define(cls))
     graph_s = np.array([a.elapsed_time(c) for a, c in ev]) * 1e-3
     fused_launch = float(graph_s.mean()) / n_launch
     fused_flops_per_launch = flops_es * N * T / n_launch
+    joined = 1 < K < 4096 and -(-N // 64) <= 4 * torch.cuda.get_device_properties(dev).multi_processor_count
 
     # The same rollout as T single-step launches (graph-captured), timed the same way. The
     # capture is taken at step 0, the step every replay starts from, so each launch's
@@ -337,7 +339,10 @@ def main():
                      "peak": PEAK_FP32_VECTOR / 1e12, "unit": "TFLOP/s",
                      "frac": fused_flops_per_launch / fused_launch / PEAK_FP32_VECTOR, "traffic": traffic.get(K),
                      "traffic_unit": "B/launch",
-                     "kernel": f"k_step<float,{cls.m},false,false,{str(shaped).lower()},{tmpl_tail}> K={K}", "launches_per_step": n_launch,
+                     "kernel": (f"k_step_ahead<float,{cls.m},false,{str(shaped).lower()},{tmpl_tail},true> K={K}" if joined else
+                                f"k_step<float,{cls.m},false,false,{str(shaped).lower()},{tmpl_tail}> K={K}"),
+                     "stretches_per_step": n_launch,
+                     "launches_per_step": -(-T // (4096 // K * K)) if joined else n_launch,
                      "launch_us_mean": fused_launch * 1e6, "flops_per_env_step": flops_es,
                      "valu_ops_per_env_step": ops_es},
         "single_step": {"env_steps_per_s": single_rate, "kernel": f"k_step<float,{cls.m},false,true,{str(shaped).lower()},{tmpl_tail}> K=1",
@@ -454,7 +459,7 @@ def plain(args):
     out["cpu_baseline"] = {"value": rates[threads], "unit": "env-steps/s", "cores": threads, "kind": "oracle",
                            "value_one_thread": rates[1],
                            "sample": f"all {N} environments x {T} steps, FP64 C oracle (OpenMP over environments)"}
-    out["note"] = "16 waves on 1024 SIMDs: launch-latency bound (63 launches per rollout)"
+    out["note"] = "16 tiles on 1024 SIMDs, two waves each: bound by the chain of one tile's steps (one launch per rollout)"
     print(json.dumps(out), flush=True)
 
 
@@ -834,18 +839,19 @@ def adjoint(args):
     # segment's steps once more with their forward quantities.
     last = H - (H - 1) // CK * CK
     traffic = recorded_adjoint_traffic()
+    few = 3 * -(-N // 64) <= 4 * torch.cuda.get_device_properties(0).multi_processor_count  # three waves per tile
     bwd_flops = step_flops * N * (H - last) + vjp_flops * N * H
     fwd_flops = step_flops * N * (H + last)
     out = {"metric": METRIC, "workload": f"adjoint_{N}x{H}", "unit": "env-steps/s", "value": N * H / (f + g),
            "n_envs": N, "horizon": H, "checkpoint_every": CK, "thrusters": m,
            "forward_ms": f * 1e3, "backward_ms": g * 1e3, "forward_env_steps_per_s": N * H / f,
            "backward_env_steps_per_s": N * H / g, "backward_over_forward": g / f,
-           "roofline": {"bound": "alu", "kernel": f"k_rollout_bwd<float,{m},false>",
+           "roofline": {"bound": "alu", "kernel": f"k_rollout_bwd{'_split' if few else ''}<float,{m},false>",
                         "achieved": bwd_flops / g / 1e12, "peak": (PEAK_FP32_VECTOR / 1e12), "unit": "TFLOP/s",
                         "frac": bwd_flops / g / 1e12 / (PEAK_FP32_VECTOR / 1e12), "flops_per_env_step": bwd_flops / (N * H),
                         "vjp_flops_per_env_step": vjp_flops, "vjp_valu_ops_per_env_step": vjp_ops,
                         "launch_ms": g * 1e3, "traffic": traffic.get("bwd"), "traffic_unit": "B/launch"},
-           "forward_roofline": {"bound": "alu", "kernel": f"k_rollout_fwd<float,{m},false>",
+           "forward_roofline": {"bound": "alu", "kernel": f"k_rollout_fwd{'_ahead' if few else ''}<float,{m},false>",
                                 "achieved": fwd_flops / f / 1e12, "peak": (PEAK_FP32_VECTOR / 1e12),
                                 "unit": "TFLOP/s", "frac": fwd_flops / f / 1e12 / (PEAK_FP32_VECTOR / 1e12),
                                 "flops_per_env_step": fwd_flops / (N * H), "traffic": traffic.get("fwd"),

@@ -488,10 +488,11 @@ mgx_status mgx_host_step_vjp(int32_t m, uint32_t batch_flags, const double* cls,
 
 typedef struct mgx_graph mgx_graph;
 
-/* Captures a rollout chunk into a HIP graph: ceil(n_steps / K) step launches of K steps
- * (the last one shorter), exactly as mgx_batch_step would enqueue them for the same
- * arguments (MGX_STEP_UNFUSED: one step per launch; MGX_STEP_STATS: statistics on the last
- * launch). Capture happens on a private stream; nothing runs and the batch is unchanged.
+/* Captures a rollout chunk into a HIP graph: ceil(n_steps / K) stretches of K steps (the
+ * last one shorter), with the results of as many mgx_batch_step calls of K steps
+ * (MGX_STEP_UNFUSED: one step per launch; MGX_STEP_STATS: statistics of the last stretch).
+ * While every class has at most a tile of 64 environments per SIMD, stretches share a launch
+ * (up to 4096 steps); otherwise each is a launch. Capture happens on a private stream; nothing runs and the batch is unchanged.
  * Each replay runs on the batch's stream and advances the batch by n_steps. Because every
  * launch reads its step from the device counter, one graph walks through a rollout-long
  * action buffer: replay r uses rows floor(t/hold) - row0 for t from the batch's step at
