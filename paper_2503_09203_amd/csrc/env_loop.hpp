@@ -229,10 +229,23 @@ __device__ __forceinline__ bool finite_(T x) {
     return x == x && abs_(x) <= (T)3.0e38;
 }
 
-// finite_ of every component of a state: the largest magnitude, NaN passing through, against
-// the bound (in float half an instruction per component instead of three).
-template <typename T, int M>
+// finite_ of every component of a state: (kJoined) the largest magnitude, NaN passing through,
+// against the bound (in float half an instruction per component instead of three), or each by
+// itself.
+template <typename T, int M, bool kJoined = true>
 __device__ __forceinline__ bool finite_state(const StateT<T, M>& s) {
+    if constexpr (!kJoined) {
+        bool fin = true;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) fin &= finite_(s.p[j]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) fin &= finite_(s.q[j]);
+#pragma unroll
+        for (int j = 0; j < 6; ++j) fin &= finite_(s.nu[j]);
+#pragma unroll
+        for (int i = 0; i < M; ++i) fin &= finite_(s.n[i]);
+        return fin;
+    }
     T m = T(0);
 #pragma unroll
     for (int j = 0; j < 3; ++j) m = __builtin_elementwise_maximum(m, abs_(s.p[j]));

@@ -234,10 +234,26 @@ __device__ __forceinline__ void restart_spread(const StationConsts& P, uint64_t 
 // for all of them, a full write latency in every step (2.34 us per step at 65,536
 // environments in calls of 100, 1.87 since). For the same reason every store is unconditional: the block
 // size divides the padded segment (launch_station), so no lane lies past it.
+//
+// Loads are indexed by a copy of the slot that the compiler cannot tell from another one. With
+// one index it formed the addresses of the state, target and counters once for their loads and
+// their stores and held them in between: 58 vector registers over the whole step, and so fewer
+// waves per SIMD (one-step launches of 6 propellers in float 186 registers, 127 now: 262,144
+// environments 19.9 -> 18.7 us, 131,072 in double 22.9 -> 16.9, five actuators with fins 15.5 ->
+// 10.8). The one-step form holds kStationWaves waves per SIMD, which bodies just beyond a step of the
+// register file reach without spills.
+template <typename T, int M, bool kFins, bool kPayload, bool kMulti>
+constexpr int kStationWaves = kMulti || kFins                ? 1
+                              : sizeof(T) == 4               ? (M <= 6 && !kPayload ? 4 : 1)
+                              : M <= (kPayload ? 2 : 6)      ? 2
+                                                             : 1;
+
 template <typename T, int M, bool kShaped, bool kFins, bool kPayload, bool kMulti>
-__global__ void __launch_bounds__(256) k_station_step(StationLaunch<T> L) {
+__global__ void __launch_bounds__(256, (kStationWaves<T, M, kFins, kPayload, kMulti>))
+    k_station_step(StationLaunch<T> L) {
     const StationArgs<T>& A = L.a;
     const int64_t env = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t el = (int64_t)blockIdx.x * blockDim.x + in_vgpr((int32_t)threadIdx.x);  // env, for the loads
     const int64_t np = A.npad;
     // Every lane loads everything and takes the steps, with no branch ahead of its loads:
     // behind a branch on the kernel arguments, each group of loads waited for another
@@ -246,7 +262,7 @@ __global__ void __launch_bounds__(256) k_station_step(StationLaunch<T> L) {
     // (they stay in the wave for the restarts).
     const bool valid = env < A.nvalid;
     StateT<T, M> s;
-    load_state<T, M>(A.state, np, env, s);
+    load_state<T, M>(A.state, np, el, s);
     // classes with fins carry the attitude's low-order words through the launch (float)
     constexpr bool kComp = kFins && std::is_same<T, float>::value;
     StateLo<T> lo;
@@ -254,28 +270,26 @@ __global__ void __launch_bounds__(256) k_station_step(StationLaunch<T> L) {
     for (int j = 0; j < 4; ++j) lo.q[j] = T(0);
     T tg[7];
 #pragma unroll
-    for (int j = 0; j < 7; ++j) tg[j] = A.tgt[j * np + env];
+    for (int j = 0; j < 7; ++j) tg[j] = A.tgt[j * np + el];
     const ClassT<T> C = class_in_vgpr<T, M, kFins>(L.cls);
     EnvT<T> E;
     T IA2[3], Brb[3];
     bool restarted = false;
     T a[M], nxt[M];
-    load_record<T, kPayload>(A.rec, np, env, C.flags, E);
-    int32_t ep = A.ep[env];
-    int32_t et = A.et[env];
+    load_record<T, kPayload>(A.rec, np, el, C.flags, E);
+    int32_t ep = A.ep[el];
+    int32_t et = A.et[el];
     if constexpr (kMulti) {
 #pragma unroll
-        for (int i = 0; i < M; ++i) nxt[i] = A.act[i * np + env];
+        for (int i = 0; i < M; ++i) nxt[i] = A.act[i * np + el];
     } else {
         // lanes without a row load the last one and take zeros. Rows as a policy returns them
         // are read where they lie: with their copy into the batch layout and two conversions
         // of the flags, a Gym step was four launches (34 us from Python, 13.5 now)
-        const int64_t ea = env < A.act_n ? env : A.act_n - 1;
+        const int64_t ea = el < A.act_n ? el : A.act_n - 1;
         const T* row = A.act + ea * A.act_env;
 #pragma unroll
         for (int i = 0; i < M; ++i) nxt[i] = row[i * A.act_thr];
-#pragma unroll
-        for (int i = 0; i < M; ++i) nxt[i] = env < A.act_n ? nxt[i] : T(0);
     }
     env_prologue<T, kPayload>(C, E, IA2, Brb);
     const int32_t n_steps = kMulti ? A.n_steps : 1;
@@ -283,7 +297,23 @@ __global__ void __launch_bounds__(256) k_station_step(StationLaunch<T> L) {
     if constexpr (kMulti) __builtin_amdgcn_s_waitcnt(0);
 #pragma unroll
     for (int i = 0; i < M; ++i) a[i] = clip1(nxt[i]);
+    if constexpr (!kMulti) {
+#pragma unroll
+        for (int i = 0; i < M; ++i) a[i] = select_(el < A.act_n, a[i], T(0));
+    }
+    // Classes with fins in double spill up to hundreds of values in a step, more operations
+    // than a wait can count past: there the row is taken at the top of its step (20 steps of
+    // 65,536 with 8 actuators 388 us, taken at the end 423).
+    constexpr bool kTakeFirst = kMulti && kFins && sizeof(T) == 8;
+    // Restarts are weighed as rare where the restart's constants would crowd the step's out of
+    // the scalar registers; one-step float launches without fins have no loop to keep them
+    // over, and are slower so (200,000 with shaped propellers 14.2 us, 13.7).
+    constexpr bool kRare = kMulti || kFins || sizeof(T) == 8;
     for (int32_t k = 0; k < n_steps; ++k) {
+        if constexpr (kTakeFirst) {
+#pragma unroll
+            for (int i = 0; i < M; ++i) a[i] = clip1(nxt[i]);
+        }
         if constexpr (kMulti) {
             // the next row, clamped to the last (a load guarded per step would make the
             // compiler wait for it before the step)
@@ -300,8 +330,9 @@ __global__ void __launch_bounds__(256) k_station_step(StationLaunch<T> L) {
         float st[kStats];  // launch statistics are not kept by the task
         renorm_attitude<T>(s, st);
 
-        // reward and termination on the state the transition ends in
-        const bool fin = finite_state<T, M>(s);
+        // reward and termination on the state the transition ends in (one-step double launches
+        // check each component by itself: 8,192 with shaped propellers 7.8 us, joined 8.2)
+        const bool fin = finite_state<T, M, kMulti || sizeof(T) == 4>(s);
         const T d0 = tg[0] - s.p[0], d1 = tg[1] - s.p[1], d2 = tg[2] - s.p[2];
         const T d = sqrt_(d0 * d0 + d1 * d1 + d2 * d2);
         T e[4];
@@ -325,9 +356,7 @@ __global__ void __launch_bounds__(256) k_station_step(StationLaunch<T> L) {
             for (int j = 0; j < 4; ++j) lo.q[j] = T(0);
         }
         const uint64_t need = __ballot(done);
-        // rare: weighed as likely, the restart's constants crowd the step's out of the scalar
-        // registers
-        if (__builtin_expect(need != 0, 0)) {
+        if (kRare ? __builtin_expect(need != 0, 0) : need != 0) {
             if (__popcll(need) <= kSpreadRestarts)
                 restart_spread<T, M>(A.P, need, (uint32_t)(A.env_off + env), (uint32_t)ep, s, tg);
             else if (done)
@@ -338,7 +367,7 @@ __global__ void __launch_bounds__(256) k_station_step(StationLaunch<T> L) {
         A.reward[fo] = r;
         A.term[fo] = term ? 1 : 0;
         A.trunc[fo] = trunc ? 1 : 0;
-        if constexpr (kMulti) {
+        if constexpr (kMulti && !kTakeFirst) {
 #pragma unroll
             for (int i = 0; i < M; ++i) a[i] = clip1(nxt[i]);
         }
