@@ -77,11 +77,19 @@ static void launch_step_body(const StepLaunch<T>& L, unsigned grid, int block, b
         constexpr bool kAheadOut = kShaped && !kFins && sizeof(T) == 4;
         if (!L.a.partials && two_waves(L.a.npad, L.a.K, kDoubleFins, n_cu) &&
             (!out || (kAheadOut && L.a.K > 32))) {
-            // Four tiles to a block from two per compute unit on, so that every SIMD holds one
-            // wave of either kind (a block's waves go round the SIMDs); fewer are spread over
-            // more units.
+            // One block per compute unit, the tiles spread over all units: a block's waves go
+            // round its unit's SIMDs, so no SIMD holds two rigid-body waves. (In blocks of four,
+            // 33,000 environments left half the units idle: 8-step launches 7.06 us, 6.49 so,
+            // 6.77 with one wave per tile.) Up to two tiles per unit, float bodies stay at one
+            // per block where the LDS of two blocks fits a unit (16-step launches of 20,000 8.61
+            // us, 8.91 in blocks of two). Where it does not (eight actuators with fins), half the
+            // blocks would wait for the others to end: 100 steps of 20,000 187 us, 96 so, 129
+            // with one wave per tile. In double, two blocks' waves share SIMDs: 56.5 us, 48.2 so.
+            constexpr size_t kUnitLds = 160 * 1024;
+            constexpr bool kTwoBlocks =
+                sizeof(T) == 4 && 2 * kAheadTiles * sizeof(AheadRing<T, M, kFins>) < kUnitLds;
             const int64_t tiles = L.a.npad / kWave;
-            const int per = tiles > 2 * (int64_t)n_cu ? kAheadTiles : 1;
+            const int per = kTwoBlocks && tiles <= 2 * (int64_t)n_cu ? 1 : (int)((tiles + n_cu - 1) / n_cu);
             const dim3 g((unsigned)((tiles + per - 1) / per)), b(2 * per * kWave);
             if (out) {
                 if constexpr (kAheadOut)

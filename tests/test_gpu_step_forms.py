@@ -1,0 +1,71 @@
+"""Step launches with two waves per tile against the one-wave form that larger batches run, at
+the sizes where the split of tiles over blocks changes, without outputs or statistics (launches
+with either take other kernels)."""
+import numpy as np
+import pytest
+
+import synth
+from paper_2503_09203_amd import mgx
+
+from test_gpu_parity import fins_class, make_batch
+
+pytestmark = pytest.mark.gpu
+
+ONE_WAVE = 65600      # more tiles than the device has SIMDs
+
+
+def _class(body):
+    base = synth.plain_class()
+    return {"plain": lambda: base, "shaped": lambda: synth.propeller_variants(base), "payload": synth.payload_class,
+            "fins": lambda: fins_class(8)}[body]()
+
+
+@pytest.mark.parametrize("body,precision", [("plain", mgx.FP32), ("shaped", mgx.FP32), ("payload", mgx.FP32),
+                                            ("fins", mgx.FP32), ("plain", mgx.FP64), ("shaped", mgx.FP64),
+                                            ("payload", mgx.FP64)])
+def test_two_wave_states_equal_the_one_wave_form(body, precision):
+    """One tile per block, two, three and four, the last block full or partly empty; one tile
+    per compute unit and one more; hand-over groups cut by the last step: the states of the same
+    environments in a batch too large for two waves, bit for bit (the same operations)."""
+    import torch as t
+    steps, got = (4, 5, 33), {}
+    for n in (ONE_WAVE, 1, 65, 16384, 16385, 33000, 49153):
+        w = synth.mixed([_class(body)], [n], steps=33, hold=3)
+        b = make_batch(w, precision)
+        s0 = b.get_state()
+        acts = b.gen_actions(12, seed=4)
+        for K in steps:
+            b.set_state(s0)
+            b.t = 0
+            b.step(acts, K, hold=3)
+            x = t.as_tensor(b.unpack_state(b.get_state())[0])
+            assert b.check() == (0, 0)
+            if n == ONE_WAVE:
+                got[K] = x
+            else:
+                assert t.equal(x, got[K][:, :n]), (n, K)
+        b.close()
+    assert not t.equal(got[4], got[5])
+
+
+def test_fin_blocks_are_resident_together():
+    """Eight actuators with fins hold the most LDS per tile. A launch of two tiles for some
+    compute units may not run its blocks in two rounds: it takes about as long as one of a tile
+    each (two rounds take twice as long; the bound is half way)."""
+    import torch as t
+    times = []
+    for n in (16384, 20000):
+        w = synth.mixed([fins_class(8)], [n], steps=1, hold=1)
+        b = make_batch(w)
+        acts = b.gen_actions(1, seed=4)
+        best = np.inf
+        for _ in range(6):
+            e0, e1 = t.cuda.Event(enable_timing=True), t.cuda.Event(enable_timing=True)
+            e0.record()
+            b.step(acts, 200, hold=1 << 20)
+            e1.record()
+            e1.synchronize()
+            best = min(best, e0.elapsed_time(e1))
+        times.append(best)
+        b.close()
+    assert times[1] < 1.5 * times[0], times
