@@ -12,6 +12,7 @@
 
 #include <new>
 
+#include "graph_split.hpp"
 #include "mgx.h"
 #include "runtime_internal.hpp"
 
@@ -65,22 +66,19 @@ extern "C" mgx_status mgx_graph_capture(mgx_batch* b, const void* actions, int64
     // stretches (K > 1) is one launch that checks the attitude's drift after every stretch, as
     // K-step launches do at their ends: the state then stays in registers over the chunk, and
     // no stretch but the first waits for a launch, its state and its record (65,536 environments
-    // x 1000 steps, K = 16: 661 us in 63 launches, 362 in one). Launches are bounded by
-    // kMaxLaunchSteps, so that no kernel holds the device for long. The stretch whose end takes
-    // statistics stays a launch of its own.
-    constexpr int32_t kMaxLaunchSteps = 4096;
+    // x 1000 steps, K = 16: 661 us in 63 launches, 362 in one).
     const bool single = (flags & MGX_STEP_UNFUSED) != 0 || K == 1;
     bool join = !single && b->mode == MGX_LAUNCH_PER_CLASS && K < kMaxLaunchSteps;
     for (int c = 0; c < b->n_classes; ++c)
         join = join && two_waves(b->npad[c], kAheadMinSteps, b->prec == MGX_FP64 && b->h_class_f[c].fin_mask != 0,
                                  b->n_cu);
-    const int32_t per = single ? 1 : join ? kMaxLaunchSteps / K * K : K;
     const bool stats = (flags & MGX_STEP_STATS) != 0;
     mgx_status st = MGX_OK;
     b->stream = cap;
+    const ChunkSplit split{n_steps, K, single, join, stats, kAheadMinSteps};
     // Only one-step launches use the step hints: a graph without any is captured once per
     // slot, and its hinted copy stays empty.
-    const bool any_single = per == 1 || n_steps % per == 1;
+    const bool any_single = split.any_single();
     for (int c = 0; c < 4 && st == MGX_OK; ++c) {
         const int p = c >> 1, h = c & 1;  // counter slot; step hints or none
         if (h && !any_single) continue;
@@ -92,10 +90,7 @@ extern "C" mgx_status mgx_graph_capture(mgx_batch* b, const void* actions, int64
         }
         int32_t launches = 0;
         for (int32_t done = 0; done < n_steps && st == MGX_OK;) {
-            int32_t k = (n_steps - done) < per ? (n_steps - done) : per;
-            if (join && stats && done + k == n_steps && k > K) k = (k - 1) / K * K;
-            // fewer steps than the two-wave form takes: stretch by stretch
-            if (join && k < kAheadMinSteps && k > K) k = K;
+            const int32_t k = split.next(done);
             st = enqueue_step(b, actions, n_rows, row0, hold, k, k < K ? k : K, stats && done + k == n_steps, nullptr,
                               nullptr, b->block, h ? b->host_t + done : -1);
             done += k;
