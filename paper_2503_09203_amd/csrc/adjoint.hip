@@ -793,7 +793,7 @@ static AdjArgs adj_args(mgx_batch* b, int c) {
     A.ckpt_buf = (char*)b->ro_ckpt_mem + P * b->state_off[c];
     A.ckpt_stride = b->state_elems;
     // tile-blocked: a class's block follows the blocks of the classes before it
-    A.seg_buf = (char*)b->ro_seg_mem + P * (size_t)2 * b->ro_ckpt * b->state_off[c];
+    A.seg_buf = (char*)b->ro_seg_mem + P * (size_t)2 * b->ro_ckpt * kSegFields * b->pad_off[c];
     A.tape_buf = (char*)b->ro_tape_mem + P * (size_t)2 * b->ro_ckpt * kTapeFields * b->pad_off[c];
     A.pos_stride = 3 * b->npad_total;
     A.misc = b->d_misc;
@@ -849,7 +849,8 @@ static mgx_status rollout_forward(mgx_batch* b, const void* actions, int64_t n_r
     hipDevice_guard guard(b->device);
     const int64_t nck = (H + ckpt_every - 1) / ckpt_every;
     const size_t P = (size_t)b->prec;
-    const size_t ck_bytes = P * (size_t)nck * b->state_elems, seg_bytes = P * (size_t)2 * ckpt_every * b->state_elems;
+    const size_t ck_bytes = P * (size_t)nck * b->state_elems;
+    const size_t seg_bytes = P * (size_t)2 * ckpt_every * kSegFields * b->npad_total;
     const size_t tape_bytes = P * (size_t)2 * ckpt_every * kTapeFields * b->npad_total;
     void* ck_mem = nullptr;
     void* seg_mem = nullptr;

@@ -281,12 +281,12 @@ struct AdjArgs {
     int64_t t0;            // global step at the start of the rollout
     void* ckpt_buf;        // class segment within each checkpoint row; row stride ckpt_stride
     int64_t ckpt_stride;   // elements per checkpoint row (state_elems)
-    // Recompute buffer (states of two segments) and tape (the kTapeLen forward quantities of
+    // Recompute buffer (attitudes and velocities of two segments) and tape (the kTapeLen forward quantities of
     // their steps and the actions' clip mask), both private to the reverse sweep and blocked
     // by 64-environment tile:
     // [tile][2 x ckpt rows][field][64 lanes], so the fields of one step of one tile lie 256 B
     // apart and a wave reaches them from one address with immediate offsets.
-    void* seg_buf;         // class block, (13+m) fields per row
+    void* seg_buf;         // class block, ten fields per row
     void* tape_buf;        // class block, kTapeLen + 1 fields per row
     void* pos;             // class segment within a position row (3 x npad); row stride pos_stride
     int64_t pos_stride;

@@ -83,3 +83,20 @@ def test_later_static_forward_invalidates_earlier_checkpoints():
     t.cuda.synchronize()
     b1.close()
     b2.close()
+
+
+@pytest.mark.parametrize("n,ckpt", [(5120, 32), (4480, 32), (5632, 32)])
+def test_static_forward_takes_what_its_rows_need(n, ckpt):
+    """The array holds what the documented formula says: checkpoints of the whole state, ten
+    fields per recompute row, 36 per tape row. Sizes near its end equal the allocating forward
+    pass; one beyond it is refused."""
+    t = torch()
+    horizon, pad, state = 64, -(-n // 64) * 64, 13 + 8
+    up = lambda x: -(-x // 256) * 256
+    need = up(4 * -(-horizon // ckpt) * state * pad) + up(4 * 2 * ckpt * 10 * pad) + 4 * 2 * ckpt * 36 * pad
+    if need > 64 << 20:
+        with pytest.raises(mgx.MgxError):
+            _run(True, n, horizon, ckpt)
+        return
+    for x, y in zip(_run(True, n, horizon, ckpt), _run(False, n, horizon, ckpt)):
+        assert t.equal(x, y)
