@@ -9,6 +9,7 @@ quadratic damping and added mass.
 from __future__ import annotations
 
 import ctypes
+import functools
 
 import numpy as np
 import torch
@@ -44,6 +45,16 @@ class DiffRollout:
         self.par_idx = torch.as_tensor(np.concatenate(par_idx, axis=1), device=dev)   # [18, N]
         self.pos_row = 3 * npad_tot
         self.par_len = 18 * npad_tot
+
+    @functools.cached_property
+    def pos_idx(self):
+        """Index map [3, N] from a row of positions (padded, class-segmented) to
+        class-concatenated environment order."""
+        pos_idx, pad_off = [], 0
+        for n, npad in zip(self.b.n, self.b.n_pad):
+            pos_idx.append(np.stack([3 * pad_off + j * npad + np.arange(n) for j in range(3)]))
+            pad_off += npad
+        return torch.as_tensor(np.concatenate(pos_idx, axis=1), device=self.b.device)
 
     def set_params(self, dlin, dquad, added):
         self._p = [t.detach().to(torch.float64).contiguous() for t in (self.mass, added, dlin, dquad, self.buoy,

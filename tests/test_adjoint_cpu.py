@@ -179,3 +179,16 @@ def test_positions_are_the_gather_of_the_padded_layout(n, n_pad):
     assert ro.positions(x).data_ptr() != x.data_ptr() and ro.positions(x).is_contiguous()
     with pytest.raises(Exception):
         ro.positions(x[:, :-1 - (n_pad[-1] - n[-1])])
+
+
+def test_position_index_map():
+    """DiffRollout.pos_idx gathers the positions' rows as positions() does."""
+    import types
+
+    import torch
+    from paper_2503_09203_amd.autograd import DiffRollout
+    ro = DiffRollout.__new__(DiffRollout)
+    ro.b = types.SimpleNamespace(n=[64, 1, 130], n_pad=[64, 64, 192], device="cpu")
+    x = torch.randn((5, 3 * 320), generator=torch.Generator().manual_seed(3))
+    assert ro.pos_idx.dtype == torch.int64 and ro.pos_idx.shape == (3, 195)
+    assert torch.equal(x[:, ro.pos_idx], ro.positions(x))
