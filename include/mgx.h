@@ -576,7 +576,8 @@ mgx_status mgx_station_step(mgx_station* s, const void* actions, int32_t n_steps
 
 /* One task step of a one-class batch (a Gym step) with the commands as a policy returns them:
  * command i of environment e < n at actions[e * env_stride + i * act_stride] (device, the
- * batch's precision, strides >= 1 in elements), nothing beyond them read. Everything else as
+ * batch's precision, strides >= 1 in elements), nothing beyond them read, and none of them in the output buffers
+ * (other environments write there while it is read). Everything else as
  * mgx_station_step with n_steps = 1; MGX_E_INVALID for a batch of several classes. */
 mgx_status mgx_station_step_rows(mgx_station* s, const void* actions, int64_t env_stride, int64_t act_stride,
                                  void* obs, void* reward, uint8_t* terminated, uint8_t* truncated, void* final_obs);

@@ -906,18 +906,25 @@ class VecStationKeeping:
         self.action_low, self.action_high = -1.0, 1.0
         self._act = self.batch.empty_actions(1)
         self._out = self.task.empty_outputs(1)
+        self._ptr = [self._out[k].data_ptr() for k in ("obs", "reward", "final_obs")]
+        self._end = [p + self._out[k].nbytes for p, k in zip(self._ptr, ("obs", "reward", "final_obs"))]
 
     def _view(self, flat):
         return flat.view(-1, self.batch.n_pad[0])[:, :self.num_envs].t()
 
     def _as_rows(self, actions):
         """True if the kernel can read ``actions`` where they lie: the batch's precision and
-        device, one row per environment, on the batch's stream."""
+        device, one row per environment, on the batch's stream, and not in the buffers that it
+        writes while other environments' rows are still to be read."""
         torch, b = _torch(), self.batch
-        return (type(actions) is torch.Tensor and actions.dtype == b.dtype and actions.device == b.device
-                and actions.shape == (self.num_envs, self.m) and min(actions.stride()) > 0
-                and actions.layout == torch.strided and not actions.is_neg()
-                and torch.cuda.current_stream(b.device) == b.stream)
+        if not (type(actions) is torch.Tensor and actions.dtype == b.dtype and actions.device == b.device
+                and actions.shape == (self.num_envs, self.m) and actions.layout == torch.strided
+                and min(actions.stride()) > 0 and not actions.is_neg()
+                and torch.cuda.current_stream(b.device) == b.stream):
+            return False
+        p = actions.data_ptr()
+        (a, b, c), (a1, b1, c1) = self._ptr, self._end
+        return not (a <= p < a1 or b <= p < b1 or c <= p < c1)
 
     def reset(self, seed=0):
         self.task.reset(seed, self._out["obs"][0])
@@ -931,9 +938,9 @@ class VecStationKeeping:
             b, o = self.batch, self._out
             np_ = b.n_pad[0]
             flags = _torch().empty((2, np_), dtype=_torch().bool, device=b.device)
-            f = flags.data_ptr()
-            _call("mgx_station_step_rows", self.task.h, actions.data_ptr(), actions.stride(0), actions.stride(1),
-                  o["obs"].data_ptr(), o["reward"].data_ptr(), f, f + np_, o["final_obs"].data_ptr())
+            f, (obs, reward, final_obs) = flags.data_ptr(), self._ptr
+            _call("mgx_station_step_rows", self.task.h, actions.data_ptr(), *actions.stride(), obs, reward, f, f + np_,
+                  final_obs)
             shape, stride = (n, STATE_FIXED + self.m), (1, np_)
             return (o["obs"].as_strided(shape, stride), o["reward"][0, :n], flags[0, :n], flags[1, :n],
                     {"final_obs": o["final_obs"].as_strided(shape, stride)})

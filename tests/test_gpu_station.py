@@ -463,3 +463,28 @@ def test_rows_entry_refuses_bad_arguments():
         assert mgx.lib().mgx_station_step_rows(st.h, x.data_ptr(), *strides, *args) == mgx.MGX_E_INVALID
     assert mgx.lib().mgx_station_step_rows(st.h, None, 6, 1, *args) == mgx.MGX_E_INVALID
     b.close()
+
+
+@pytest.mark.parametrize("key", ["obs", "final_obs"])
+def test_commands_taken_from_the_outputs_are_read_before_they_are_written(key):
+    """Commands that are a view of the returned observations, shifted by many environments: the
+    step that writes those buffers uses what they held before it (equal to a copy's step). The
+    batch is larger than the device runs at once."""
+    t = torch()
+    m, n, shift = 6, 786432, 262144
+    cls = synth.draw_class(m, 0)
+    p = synth.EnvParams(mass=np.full(n, cls.mass), buoy=np.full(n, cls.buoy), current=np.zeros((3, n)),
+                        **{k: np.repeat(np.asarray(getattr(cls, k))[:, None], n, 1) for k in ("added", "dlin", "dquad")})
+    out = []
+    for copied in (False, True):
+        env = mgx.VecStationKeeping(cls, p, n)
+        obs, _ = env.reset(5)
+        info = env.step(t.zeros((n, m), device="cuda"))[4]
+        src = obs if key == "obs" else info["final_obs"]
+        if key == "final_obs":
+            src.copy_(obs)
+        x = t.as_strided(src, (n, m), (1, n), 2 * n - shift)     # rows 1 .. m, `shift` environments back
+        out.append([y.clone() for y in env.step(x.clone() if copied else x)[:3]])
+        env.close()
+    for a, b in zip(*out):
+        assert t.equal(a, b)
