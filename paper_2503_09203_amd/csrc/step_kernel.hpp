@@ -71,25 +71,32 @@ static void launch_step_body(const StepLaunch<T>& L, unsigned grid, int block, b
     if constexpr (!kDoubleFins) {
         // Launches with outputs: both waves store, and those of the short hand-over groups only
         // wait for each other (4,571 environments with the trajectory: 8 steps 8.4 -> 9.3 us,
-        // 64 steps 42.6 -> 45.1), so they take two waves only for longer launches of the
-        // float bodies with more to do per step (shaped 48.9 -> 45.6, payload 77 -> 71 for 64
-        // steps; at 32 and fewer shaped 26.6 -> 27.4).
+        // 64 steps 42.6 -> 45.1), so they take two waves only for longer launches of the float
+        // bodies with more to do per step, up to two tiles per compute unit. The thrust of seven
+        // or eight actuators pays for the hand-over by itself (64 steps of 1,024 to 32,768, eight
+        // shaped: 6 to 8% less). With fewer, what pays is the command rows, which wait for
+        // another wave's stores no more: 64 steps of six, a row every step 20 to 30% less, every
+        // 4 steps 4 to 9%, every 10 with a payload 3% less and without 2% less to 1% more, held
+        // throughout up to 5% more; of four, a row every step 10% less, every 4 steps 2 to 7%
+        // more.
         constexpr bool kAheadOut = kShaped && !kFins && sizeof(T) == 4;
+        constexpr int64_t kOutHold = M >= 7 ? INT64_MAX : M == 6 ? (kPayload ? 16 : 8) : 1;
         if (!L.a.partials && two_waves(L.a.npad, L.a.K, kDoubleFins, n_cu) &&
-            (!out || (kAheadOut && L.a.K > 32))) {
+            (!out || (kAheadOut && L.a.K > 32 && L.a.hold <= kOutHold && L.a.npad / kWave <= 2 * (int64_t)n_cu))) {
             // One block per compute unit, the tiles spread over all units: a block's waves go
             // round its unit's SIMDs, so no SIMD holds two rigid-body waves. (In blocks of four,
             // 33,000 environments left half the units idle: 8-step launches 7.06 us, 6.49 so,
-            // 6.77 with one wave per tile.) Up to two tiles per unit, float bodies stay at one
-            // per block where the LDS of two blocks fits a unit (16-step launches of 20,000 8.61
-            // us, 8.91 in blocks of two). Where it does not (eight actuators with fins), half the
+            // 6.77 with one wave per tile.) Up to two tiles per unit, float bodies without outputs
+            // stay at one per block where the LDS of two blocks fits a unit (16-step launches of
+            // 20,000 8.61 us, 8.91 in blocks of two; with a trajectory, 64 steps 54.3, 49.1 in
+            // blocks of two). Where it does not (eight actuators with fins), half the
             // blocks would wait for the others to end: 100 steps of 20,000 187 us, 96 so, 129
             // with one wave per tile. In double, two blocks' waves share SIMDs: 56.5 us, 48.2 so.
             constexpr size_t kUnitLds = 160 * 1024;
             constexpr bool kTwoBlocks =
                 sizeof(T) == 4 && 2 * kAheadTiles * sizeof(AheadRing<T, M, kFins>) < kUnitLds;
             const int64_t tiles = L.a.npad / kWave;
-            const int per = kTwoBlocks && tiles <= 2 * (int64_t)n_cu ? 1 : (int)((tiles + n_cu - 1) / n_cu);
+            const int per = kTwoBlocks && !out && tiles <= 2 * (int64_t)n_cu ? 1 : (int)((tiles + n_cu - 1) / n_cu);
             const dim3 g((unsigned)((tiles + per - 1) / per)), b(2 * per * kWave);
             if (out) {
                 if constexpr (kAheadOut)

@@ -1,6 +1,5 @@
 """Step launches with two waves per tile against the one-wave form that larger batches run, at
-the sizes where the split of tiles over blocks changes, without outputs or statistics (launches
-with either take other kernels)."""
+the sizes where the split of tiles over blocks changes and at the limits of their rules."""
 import numpy as np
 import pytest
 
@@ -46,6 +45,38 @@ def test_two_wave_states_equal_the_one_wave_form(body, precision):
                 assert t.equal(x, got[K][:, :n]), (n, K)
         b.close()
     assert not t.equal(got[4], got[5])
+
+
+@pytest.mark.parametrize("m,body", [(1, "shaped"), (6, "shaped"), (6, "payload"), (8, "shaped"), (8, "payload")])
+def test_two_wave_outputs_equal_the_one_wave_form(m, body):
+    """Launches with trajectory and wrenches on both sides of the two-wave form's limits (33
+    steps; the longest hold per actuator count; two tiles per compute unit): states, trajectories
+    and wrenches of a batch too large for it, bit for bit."""
+    import torch as t
+    from dataclasses import replace
+    cls = synth.draw_class(m)
+    cls = synth.propeller_variants(cls) if body == "shaped" else replace(cls, rg=np.array([0.015625, -0.0078125, 0.015625]))
+    cases, got = ((32, 1), (33, 1), (34, 2), (35, 8), (35, 9), (35, 16), (36, 17), (33, 100)), {}
+    for n in (ONE_WAVE, 65, 16385, 32768, 32769):
+        w = synth.mixed([cls], [n], steps=36, hold=1)
+        b = make_batch(w)
+        s0 = b.get_state()
+        acts = b.gen_actions(36, seed=4)
+        L = b.layout
+        for K, hold in cases:
+            b.set_state(s0)
+            b.t = 0
+            traj = t.zeros((K, L.state_elems), device=b.device)
+            forces = t.zeros((K, L.force_row_elems), device=b.device)
+            b.step(acts, K, hold=hold, traj=traj, forces=forces)
+            x = [t.as_tensor(b.unpack_state(b.get_state())[0]), traj.view(K, 13 + m, -1), forces.view(K, 12, -1)]
+            assert b.check() == (0, 0)
+            if n == ONE_WAVE:
+                got[K, hold] = x = [y[..., :32769].clone() for y in x]
+                assert x[1].abs().max() > 0 and x[2].abs().max() > 0
+            else:
+                assert all(t.equal(y[..., :n], z[..., :n]) for y, z in zip(x, got[K, hold])), (n, K, hold)
+        b.close()
 
 
 def test_fin_blocks_are_resident_together():
