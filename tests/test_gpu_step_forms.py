@@ -79,6 +79,36 @@ def test_two_wave_outputs_equal_the_one_wave_form(m, body):
         b.close()
 
 
+@pytest.mark.parametrize("body,precision", [("plain", mgx.FP64), ("shaped", mgx.FP64), ("payload", mgx.FP64),
+                                            ("fins", mgx.FP64), ("fins", mgx.FP32), ("payload", mgx.FP32)])
+@pytest.mark.parametrize("n,K,n_steps", [(70, 2, 7), (130, 16, 100), (33000, 3, 17)])
+def test_joined_stretches_equal_their_launches(n, K, n_steps, body, precision):
+    """A captured chunk without statistics, whose stretches share launches, against its K-step
+    launches, replayed twice; attitudes start off the unit sphere, so that the drift checks
+    between the stretches renormalise."""
+    import torch as t
+    w = synth.mixed([_class(body)], [n])
+    got = []
+    for captured in (True, False):
+        b = make_batch(w, precision)
+        x = np.array(b.unpack_state(b.get_state().cpu().numpy())[0])
+        x[3:7] *= 1.2
+        b.set_state(t.tensor(b.pack_state([x]), dtype=b.dtype, device=b.device))
+        acts = b.gen_actions((2 * n_steps + 4) // 5, seed=4)
+        if captured:
+            g = b.capture(acts, n_steps, K, hold=5)
+            g.replay()
+            g.replay()
+        else:
+            for r in range(2):
+                for k in range(0, n_steps, K):
+                    b.step(acts, min(K, n_steps - k), hold=5)
+        got.append((b.get_state(), b.t))
+        assert b.check() == (0, 0)
+        b.close()
+    assert got[0][1] == got[1][1] == 2 * n_steps and t.equal(got[0][0], got[1][0])
+
+
 def test_fin_blocks_are_resident_together():
     """Eight actuators with fins hold the most LDS per tile. A launch of two tiles for some
     compute units may not run its blocks in two rounds: it takes about as long as one of a tile
