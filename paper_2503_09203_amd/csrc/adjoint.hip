@@ -717,12 +717,16 @@ __global__ void __launch_bounds__(3 * kWave) k_rollout_bwd_split(AdjArgs A, Clas
             return hipErrorInvalidValue; \
     }
 
-// Whether the three waves of every tile find a SIMD each. Up to there the three-wave forms are
-// faster (forward pass of 16,384 x 128 90 against 105 us, in double 89 against 98 for
-// 16,384 x 64; backward of 8192 x 256 275 against 318); beyond, the SIMDs fill with whole tiles
-// and the hand-over only adds work (forward of 65,536 x 64 168 against 149; in double 169
-// against 145 for 32,768 x 64).
-static bool wave_per_simd(int64_t npad, int n_cu) { return 3 * (npad / kWave) <= 4 * (int64_t)n_cu; }
+// Whether every block of three waves finds its SIMDs at once. Beyond, the SIMDs fill with whole
+// tiles and the hand-over only adds work (forward of 65,536 x 64 168 against 149 us). Kernels in
+// double hold one wave per SIMD, and a second block of three does not fit the four SIMDs of a
+// compute unit: with more tiles than units, blocks would wait for others to end (forward of
+// 18,000 x 128 in double 30% slower than in two waves).
+template <typename T>
+static bool three_waves_fit(int64_t npad, int n_cu) {
+    const int64_t tiles = npad / kWave;
+    return sizeof(T) == 8 ? tiles <= n_cu : 3 * tiles <= 4 * (int64_t)n_cu;
+}
 
 template <typename T>
 hipError_t launch_rollout_fwd(const AdjArgs& A, const ClassT<T>& C, int m, bool shaped, int n_cu, hipStream_t s) {
@@ -732,7 +736,9 @@ hipError_t launch_rollout_fwd(const AdjArgs& A, const ClassT<T>& C, int m, bool 
     // 0.180 against 0.171 ms at 8192 x 256 with 8 thrusters and two waves per tile)
     if (A.npad % kWave != 0) return hipErrorInvalidValue;
     const unsigned grid = (unsigned)(A.npad / kWave);
-    if (wave_per_simd(A.npad, n_cu)) {
+    // A rollout of one segment ends when that segment's tape is whole, which the wave that
+    // writes it starts later in three waves (16,384 x 16 22 us, 20 in two; x 48 43, 48 in two).
+    if (three_waves_fit<T>(A.npad, n_cu) && A.H > A.ckpt) {
         const unsigned block = 3 * kWave;
 #define KERNEL k_rollout_fwd_ahead
         MGX_ADJ_SWITCH
@@ -746,20 +752,46 @@ hipError_t launch_rollout_fwd(const AdjArgs& A, const ClassT<T>& C, int m, bool 
     return hipGetLastError();
 }
 
+// Two waves per tile where three do not fit, and in float for very short rollouts (steps are
+// handed over in groups: 4 steps of 8,192 environments up to 8% slower in three waves, 8 steps
+// up to 9% faster).
+template <typename T, int M, bool kShaped>
+static void launch_bwd(const AdjArgs& A, const ClassT<T>& C, int n_cu, hipStream_t s) {
+    const dim3 grid((unsigned)(A.npad / kWave));
+    // In double with seven or eight actuators the two-wave form spills, and three waves are
+    // faster at every size (65,536 x 64 half the time).
+    constexpr bool kAlways = sizeof(T) == 8 && M >= 7;
+    if constexpr (!kAlways) {
+        if (!three_waves_fit<T>(A.npad, n_cu) || (sizeof(T) == 4 && A.H < 8)) {
+            hipLaunchKernelGGL((k_rollout_bwd<T, M, kShaped>), grid, dim3(2 * kWave), 0, s, A, C);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_rollout_bwd_split<T, M, kShaped>), grid, dim3(3 * kWave), 0, s, A, C);
+}
+
+#define MGX_BWD_CASE(MM)                                          \
+    case MM:                                                      \
+        if (shaped)                                               \
+            launch_bwd<T, MM, true>(A, C, n_cu, s);               \
+        else                                                      \
+            launch_bwd<T, MM, false>(A, C, n_cu, s);              \
+        break;
+
 template <typename T>
 hipError_t launch_rollout_bwd(const AdjArgs& A, const ClassT<T>& C, int m, bool shaped, int n_cu, hipStream_t s) {
     if (A.npad % kWave != 0) return hipErrorInvalidValue;
-    const unsigned grid = (unsigned)(A.npad / kWave);
-    if (wave_per_simd(A.npad, n_cu)) {
-        const unsigned block = 3 * kWave;
-#define KERNEL k_rollout_bwd_split
-        MGX_ADJ_SWITCH
-#undef KERNEL
-    } else {
-        const unsigned block = 2 * kWave;
-#define KERNEL k_rollout_bwd
-        MGX_ADJ_SWITCH
-#undef KERNEL
+    switch (m) {
+        MGX_BWD_CASE(1)
+        MGX_BWD_CASE(2)
+        MGX_BWD_CASE(3)
+        MGX_BWD_CASE(4)
+        MGX_BWD_CASE(5)
+        MGX_BWD_CASE(6)
+        MGX_BWD_CASE(7)
+        MGX_BWD_CASE(8)
+        default:
+            return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }

@@ -247,3 +247,30 @@ def test_forward_rows_ahead_at_their_edges(H_, hold, ckpt, n, precision):
         p = b.unpack_state(b.get_state().cpu().numpy())[0][:3]
         assert np.array_equal(out[0][0][k], p), k
     b.close()
+
+
+@pytest.mark.parametrize("m,precision", [(6, mgx.FP32), (6, mgx.FP64), (8, mgx.FP64)])
+@pytest.mark.parametrize("H_,ckpt", [(7, 3), (8, 3), (8, 8), (9, 8)])
+def test_wave_splits_at_the_limits_of_their_rules(H_, ckpt, m, precision):
+    """The forward and backward passes choose two or three waves per tile by tiles, horizon,
+    checkpoints, precision and actuators: positions and gradients of the first environments of
+    batches on both sides of every limit, bit for bit (the same operations in the same order)."""
+    t = torch()
+    from paper_2503_09203_amd.autograd import DiffRollout
+    got = []
+    for n in (65, 16384, 16385, 21824, 21825):
+        w = synth.mixed([synth.draw_class(m)], [n], steps=H_, hold=1)
+        b = mgx.Batch(w.classes, w.n_envs, w.dt, precision)
+        init = t.tensor(b.pack_state([w.state[0].stacked()]), dtype=b.dtype, device=b.device)
+        a = b.gen_actions(H_, seed=4).requires_grad_()
+        par = [t.tensor(np.ascontiguousarray(x), dtype=t.float64, device=b.device, requires_grad=True)
+               for x in (w.params.dlin, w.params.dquad, w.params.added)]
+        ro = DiffRollout(b, w.params, init, H_, ckpt=ckpt)
+        pos = ro.positions(ro(a, *par))
+        (pos * pos).sum().backward()
+        got.append([pos.detach()[:, :, :65], a.grad.view(H_, m, -1)[:, :, :65], *(p.grad[:, :65] for p in par)])
+        b.close()
+    for other in got[1:]:
+        for x, y in zip(got[0], other):
+            assert t.equal(x, y)
+    assert all(x.abs().max() > 0 for x in got[0])
