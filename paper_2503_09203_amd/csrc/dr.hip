@@ -234,6 +234,22 @@ __global__ void __launch_bounds__(kDrWaves * kWave) k_dr_resample(mgx_dr_spec sp
     }
 }
 
+// The same by one lane per environment, for payload classes with more than kDrPayloadTilesPerCu
+// tiles per compute unit: the inversion's registers leave a unit one block, seven of whose waves
+// wait for the one that inverts (32,768 environments 24.2 us in tiles, 28.7 by lanes; 65,536 46
+// and 39; 262,144 172 and 70). The other classes draw faster in tiles at every size.
+constexpr int kDrPayloadTilesPerCu = 2;
+
+template <typename T>
+__global__ void k_dr_resample_lane(mgx_dr_spec spec, DrNominal nom, const ClassDesc64* cls, int ci, double dt, T* rec,
+                                   int64_t npad, int64_t env_off, const int64_t* ids, int64_t n_ids, uint64_t seed,
+                                   uint64_t epoch, int32_t* err) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= n_ids) return;
+    const int64_t e = ids ? ids[t] : t;
+    dr_resample_one<T>(spec, nom, cls[ci], dt, rec, npad, env_off, e, seed, epoch, err);
+}
+
 // Masked redraw: the environments e < n whose mask byte is set, at epochs[e] (spread over the
 // wave, above).
 template <typename T>
@@ -321,8 +337,13 @@ static void launch_resample(mgx_batch* b, const mgx_dr_spec& spec, const double*
                            nom, b->d_classdesc, c, b->dt, (T*)b->seg_rec(c), b->npad[c], b->env_off[c], nid, seed, mask,
                            epochs, &b->d_misc->err);
     else {
-        const dim3 grid((unsigned)((nid + kWave - 1) / kWave)), block(kDrWaves * kWave);
-        if (b->h_class_f[c].payload)
+        const int64_t tiles = (nid + kWave - 1) / kWave;
+        const dim3 grid((unsigned)tiles), block(kDrWaves * kWave);
+        if (b->h_class_f[c].payload && tiles > kDrPayloadTilesPerCu * (int64_t)b->n_cu)
+            hipLaunchKernelGGL(k_dr_resample_lane<T>, dim3((unsigned)((nid + 127) / 128)), dim3(128), 0, b->stream, spec,
+                               nom, b->d_classdesc, c, b->dt, (T*)b->seg_rec(c), b->npad[c], b->env_off[c], ids, nid,
+                               seed, epoch, &b->d_misc->err);
+        else if (b->h_class_f[c].payload)
             hipLaunchKernelGGL((k_dr_resample<T, true>), grid, block, 0, b->stream, spec, nom, b->d_classdesc, c, b->dt,
                                (T*)b->seg_rec(c), b->npad[c], b->env_off[c], ids, nid, seed, epoch, &b->d_misc->err);
         else

@@ -108,6 +108,22 @@ __global__ void __launch_bounds__(kResetWaves * kWave) k_reset_seeded(T* state, 
     for (int r = j; r < 3 + m; r += kResetWaves) state[(r < 3 ? r : kStateFixed + r - 3) * np + e] = (T)0;
 }
 
+// The same by one lane per environment, for calls of more than kResetTilesPerCu tiles per compute
+// unit: their lanes fill the device by themselves, and the tiles' five waves and their exchange
+// only add work (98,304 environments 8.25 us in tiles, 8.8 by lanes; 131,072 10.5 and 9.0; 262,144
+// 18.8 and 15.9).
+constexpr int kResetTilesPerCu = 6;
+
+template <typename T>
+__global__ void k_reset_seeded_lane(T* state, int m, int32_t npad, int64_t env_off, int64_t n_local, const int64_t* ids,
+                                    int64_t n_ids, uint64_t seed) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= n_ids) return;
+    const int64_t e = ids ? ids[t] : t;
+    if (e < 0 || e >= n_local) return;
+    seeded_state<T>((uint64_t)(env_off + e), seed, m, state, npad, e);
+}
+
 template <typename T>
 __global__ void k_reset_copy(T* state, const T* tmpl, int m, int32_t npad, const int64_t* ids, int64_t n_ids) {
     int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -196,10 +212,15 @@ hipError_t launch_init_padding(T* state_seg, T* rec_seg, int m, int32_t npad, in
 
 template <typename T>
 hipError_t launch_reset_seeded(T* state_seg, int m, int32_t npad, int64_t env_off, int64_t n_local,
-                               const int64_t* d_local_ids, int64_t n_ids, uint64_t seed, hipStream_t s) {
+                               const int64_t* d_local_ids, int64_t n_ids, uint64_t seed, int n_cu, hipStream_t s) {
     if (n_ids <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_reset_seeded<T>, dim3((unsigned)((n_ids + kWave - 1) / kWave)), dim3(kResetWaves * kWave), 0,
-                       s, state_seg, m, npad, env_off, n_local, d_local_ids, n_ids, seed);
+    const int64_t tiles = (n_ids + kWave - 1) / kWave;
+    if (tiles <= kResetTilesPerCu * (int64_t)n_cu)
+        hipLaunchKernelGGL(k_reset_seeded<T>, dim3((unsigned)tiles), dim3(kResetWaves * kWave), 0, s, state_seg, m,
+                           npad, env_off, n_local, d_local_ids, n_ids, seed);
+    else
+        hipLaunchKernelGGL(k_reset_seeded_lane<T>, dim3((unsigned)((n_ids + 255) / 256)), dim3(256), 0, s, state_seg, m,
+                           npad, env_off, n_local, d_local_ids, n_ids, seed);
     return hipGetLastError();
 }
 
@@ -225,7 +246,7 @@ hipError_t launch_gen_actions(T* out_seg, int m, int32_t npad, int64_t n_valid, 
     template hipError_t launch_env_setup<T>(ParamPtrs, int64_t, int64_t, int32_t, const ClassDesc64*, int, double,   \
                                             T*, int32_t*, hipStream_t);                                               \
     template hipError_t launch_init_padding<T>(T*, T*, int, int32_t, int64_t, hipStream_t, int);                    \
-    template hipError_t launch_reset_seeded<T>(T*, int, int32_t, int64_t, int64_t, const int64_t*, int64_t, uint64_t, \
+    template hipError_t launch_reset_seeded<T>(T*, int, int32_t, int64_t, int64_t, const int64_t*, int64_t, uint64_t, int, \
                                                hipStream_t);                                                          \
     template hipError_t launch_reset_copy<T>(T*, const T*, int, int32_t, const int64_t*, int64_t, hipStream_t);     \
     template hipError_t launch_gen_actions<T>(T*, int, int32_t, int64_t, int64_t, int64_t, int64_t, int64_t,        \

@@ -317,7 +317,7 @@ hipError_t launch_check_params(ParamPtrs p, int64_t env_off, int64_t n, const Cl
                                int32_t* err, hipStream_t s);
 template <typename T>
 hipError_t launch_reset_seeded(T* state_seg, int m, int32_t npad, int64_t env_off, int64_t n_local,
-                               const int64_t* d_local_ids, int64_t n_ids, uint64_t seed, hipStream_t s);
+                               const int64_t* d_local_ids, int64_t n_ids, uint64_t seed, int n_cu, hipStream_t s);
 template <typename T>
 hipError_t launch_reset_copy(T* state_seg, const T* tmpl_seg, int m, int32_t npad, const int64_t* d_local_ids,
                              int64_t n_ids, hipStream_t s);

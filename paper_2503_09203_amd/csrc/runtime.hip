@@ -570,7 +570,7 @@ extern "C" mgx_status mgx_batch_reset(mgx_batch* b, const int64_t* env_ids, int6
                                                     b->m[c], (int32_t)b->npad[c], ids, nid, b->stream));
             } else {
                 HIP_TRY(b, launch_reset_seeded<float>((float*)b->seg_state(c), b->m[c], (int32_t)b->npad[c], b->env_off[c],
-                                                      b->n[c], ids, nid, seed, b->stream));
+                                                      b->n[c], ids, nid, seed, b->n_cu, b->stream));
             }
         } else {
             if (init_state) {
@@ -579,7 +579,7 @@ extern "C" mgx_status mgx_batch_reset(mgx_batch* b, const int64_t* env_ids, int6
                                                      (int32_t)b->npad[c], ids, nid, b->stream));
             } else {
                 HIP_TRY(b, launch_reset_seeded<double>((double*)b->seg_state(c), b->m[c], (int32_t)b->npad[c],
-                                                       b->env_off[c], b->n[c], ids, nid, seed, b->stream));
+                                                       b->env_off[c], b->n[c], ids, nid, seed, b->n_cu, b->stream));
             }
         }
     }

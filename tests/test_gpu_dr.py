@@ -203,3 +203,27 @@ def test_tiles_draw_alike_for_lists_and_whole_batches(n, make):
         assert b.check() == (0, 0)
         b.close()
     assert t.equal(out[0][0], out[1][0]) and t.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("make,n,step", [("plain", 98368, 49152), ("payload", 32832, 16384)])
+@pytest.mark.parametrize("precision", [mgx.FP32, mgx.FP64])
+def test_large_batches_draw_as_their_parts(make, n, step, precision):
+    """Whole batches one tile beyond the sizes that seeded states (payload redraws) take in tiles,
+    against the same environments in lists small enough for tiles, bit for bit."""
+    t = torch()
+    cls = synth.payload_class() if make == "payload" else synth.plain_class()
+    nominal = nominal_of(cls)[None]
+    out = []
+    for parts in (1, 0):
+        plan = mgx.mgx_batch_plan([mgx.mgx_class_define(cls)], [n], 0.01, precision)
+        rec = t.zeros(plan.record_elems, dtype=t.float32 if precision == mgx.FP32 else t.float64, device="cuda")
+        b = mgx.Batch([cls], [n], 0.01, precision, record=rec)
+        b.resample(SPEC, nominal, seed=9, epoch=1)
+        b.reset(seed=5)
+        for ids in [np.arange(k, min(n, k + step)) for k in range(0, n, step)] if parts else [None]:
+            b.resample(SPEC, nominal, env_ids=ids, seed=9, epoch=2)
+            b.reset(env_ids=ids, seed=4)
+        out.append((rec.clone(), b.get_state()))
+        assert b.check() == (0, 0)
+        b.close()
+    assert t.equal(out[0][0], out[1][0]) and t.equal(out[0][1], out[1][1])
