@@ -536,7 +536,12 @@ __device__ __forceinline__ void env_steps(const StepArgs& A, const ClassT<T>& Cs
     T IA2[3], Brb[3];
     env_prologue<T, kPayload>(C, E, IA2, Brb);
     if constexpr (kSingle) {
-        const StateT<T, M> s_in = s;
+        // The state a wrong expectation starts again from: kept, or where the body spills (payload
+        // and fins in double) loaded again, 13 + m values less over the step (single steps of 131,072
+        // with eight actuators 47.1 us, 42.9).
+        constexpr bool kReload = kFins && kPayload && sizeof(T) == 8;
+        StateT<T, M> s_in;
+        if constexpr (!kReload) s_in = s;
         step_body<T, M, false, kShaped, kFins, kPayload, kComp>(C, E, IA2, Brb, s, cur, nullptr, &lo);
         const int64_t tc = uniform64(t_lane);
         if (tc != A.t_hint) {
@@ -548,7 +553,19 @@ __device__ __forceinline__ void env_steps(const StepArgs& A, const ClassT<T>& Cs
             const volatile T* p0 = abase + clamp_row(r) * rstride;
 #pragma unroll
             for (int i = 0; i < M; ++i) cur[i] = clip1((T)p0[i * np]);
-            s = s_in;
+            if constexpr (kReload) {
+                const volatile T* V = S;
+#pragma unroll
+                for (int j = 0; j < 3; ++j) s.p[j] = V[j * np + envl];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) s.q[j] = V[(3 + j) * np + envl];
+#pragma unroll
+                for (int j = 0; j < 6; ++j) s.nu[j] = V[(7 + j) * np + envl];
+#pragma unroll
+                for (int i = 0; i < M; ++i) s.n[i] = V[(kStateFixed + i) * np + envl];
+            } else {
+                s = s_in;
+            }
 #pragma unroll
             for (int j = 0; j < 4; ++j) lo.q[j] = T(0);
             step_body<T, M, false, kShaped, kFins, kPayload, kComp>(C, E, IA2, Brb, s, cur, nullptr, &lo);

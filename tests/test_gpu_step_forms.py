@@ -109,6 +109,38 @@ def test_joined_stretches_equal_their_launches(n, K, n_steps, body, precision):
     assert got[0][1] == got[1][1] == 2 * n_steps and t.equal(got[0][0], got[1][0])
 
 
+@pytest.mark.parametrize("body,precision", [("plain", mgx.FP32), ("payload fins", mgx.FP64)])
+def test_single_steps_replayed_at_other_steps(body, precision):
+    """Single steps captured by the caller carry the steps of their capture; replayed later, they
+    start again on the rows that the device counter names. Against the same steps one by one."""
+    import torch as t
+    from dataclasses import replace
+    cls = synth.plain_class() if body == "plain" else replace(fins_class(8), rg=np.array([0.015625, -0.0078125, 0.015625]))
+    w = synth.mixed([cls], [130], steps=8, hold=1)
+    got, side = [], t.cuda.Stream()
+    for captured in (True, False):
+        with t.cuda.stream(side):
+            b = make_batch(w, precision)
+            acts = b.gen_actions(8, seed=4)
+            t.cuda.synchronize()
+            if captured:
+                g = t.cuda.CUDAGraph()
+                with t.cuda.graph(g, stream=side):
+                    b.step(acts, 1, hold=1)
+                    b.step(acts, 1, hold=1)
+                for _ in range(4):
+                    g.replay()
+            else:
+                for _ in range(8):
+                    b.step(acts, 1, hold=1)
+            state = b.get_state().clone()
+        t.cuda.synchronize()
+        got.append(state)
+        assert b.check() == (0, 0)
+        b.close()
+    assert t.equal(got[0], got[1])
+
+
 def test_fin_blocks_are_resident_together():
     """Eight actuators with fins hold the most LDS per tile. A launch of two tiles for some
     compute units may not run its blocks in two rounds: it takes about as long as one of a tile

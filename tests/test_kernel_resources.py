@@ -55,3 +55,9 @@ def test_station_kernels_hold_their_waves():
     for name in ("fLi6ELb0ELb0ELb0ELb1E", "fLi6ELb1ELb0ELb1ELb1E", "fLi8ELb0ELb0ELb0ELb1E"):
         k, = (v for key, v in kernels.items() if key.startswith("_ZN3mgx14k_station_stepI" + name))
         assert k[".vgpr_count"] <= 256, (name, k[".vgpr_count"])
+
+
+def test_single_steps_with_payload_and_fins_in_double_spill_no_more():
+    """The largest one-step body: its spills are memory traffic of every step."""
+    k, = (v for key, v in _kernels().items() if key.startswith("_ZN3mgx6k_stepIdLi8ELb0ELb1ELb1ELb1ELb1E"))
+    assert k[".vgpr_spill_count"] <= 96, k[".vgpr_spill_count"]
