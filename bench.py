@@ -284,13 +284,14 @@ def main():
 
     # Fused kernel: HIP events on the batch's stream around every graph replay (the rollout's
     # n_launch stretches of K steps). Up to a 64-environment tile per SIMD the graph joins up
-    # to 4096 steps of stretches in a launch; beyond, each stretch is a launch. The figures are
-    # per stretch = elapsed / n_launch, so gaps between launches count against the kernel.
+    # to 4096 steps of stretches in a launch; beyond, each stretch is a launch. Times per
+    # stretch and per launch = elapsed / their number, so gaps count against the kernel.
     flops_es, ops_es = mgx.mgx_class_step_cost(mgx.mgx_class_define(cls))
     graph_s = np.array([a.elapsed_time(c) for a, c in ev]) * 1e-3
     fused_launch = float(graph_s.mean()) / n_launch
     fused_flops_per_launch = flops_es * N * T / n_launch
     joined = 1 < K < 4096 and -(-N // 64) <= 4 * torch.cuda.get_device_properties(dev).multi_processor_count
+    n_joined = -(-T // (4096 // K * K)) if joined else n_launch
 
     # The same rollout as T single-step launches (graph-captured), timed the same way. The
     # capture is taken at step 0, the step every replay starts from, so each launch's
@@ -342,8 +343,8 @@ def main():
                      "kernel": (f"k_step_ahead<float,{cls.m},false,{str(shaped).lower()},{tmpl_tail},true> K={K}" if joined else
                                 f"k_step<float,{cls.m},false,false,{str(shaped).lower()},{tmpl_tail}> K={K}"),
                      "stretches_per_step": n_launch,
-                     "launches_per_step": -(-T // (4096 // K * K)) if joined else n_launch,
-                     "launch_us_mean": fused_launch * 1e6, "flops_per_env_step": flops_es,
+                     "stretch_us_mean": fused_launch * 1e6, "launches_per_step": n_joined,
+                     "launch_us_mean": fused_launch * n_launch / n_joined * 1e6, "flops_per_env_step": flops_es,
                      "valu_ops_per_env_step": ops_es},
         "single_step": {"env_steps_per_s": single_rate, "kernel": f"k_step<float,{cls.m},false,true,{str(shaped).lower()},{tmpl_tail}> K=1",
                         "launch_us_mean": single_launch * 1e6,
@@ -443,7 +444,7 @@ def plain(args):
         b.close()
         ref, _, _ = oracle.rollout(envs, x0.copy(), a_host, HOLD, T)
         err = parity_errors(final, oracle.unpack_state(ref, cls.m))
-        out[name] = {"ms_per_rollout": sec * 1e3, "env_steps_per_s": N * T / sec, "launch_us_mean": sec / -(-T // K) * 1e6,
+        out[name] = {"ms_per_rollout": sec * 1e3, "env_steps_per_s": N * T / sec, "stretch_us_mean": sec / -(-T // K) * 1e6,
                      "parity_max_err": float(err.max()), "tolerance": 1e-9 if prec == mgx.FP64 else 1e-3,
                      "pass": bool(err.max() <= (1e-9 if prec == mgx.FP64 else 1e-3)), "envs_checked": N}
     threads = oracle.get_threads()

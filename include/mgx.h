@@ -401,7 +401,9 @@ mgx_status mgx_gen_actions(mgx_batch* b, void* out, int64_t rows, int64_t row_of
 typedef struct {
     int32_t mode;         /* MGX_LAUNCH_* */
     int32_t K;            /* steps per launch used when a call passes K = 0 */
-    int32_t block;        /* threads per block (64, 128 or 256) */
+    int32_t block;        /* threads per block (64, 128 or 256); without effect on launches that
+                             run two waves per tile (4 steps or more, at most a tile of 64
+                             environments per SIMD), which choose their own */
     int32_t grid_per_cu;  /* persistent mode: blocks per compute unit */
     double us_per_chunk;  /* autotuner: measured time of one chunk with this shape */
     int32_t candidates;   /* autotuner: shapes measured */
@@ -420,8 +422,9 @@ mgx_status mgx_batch_set_shape(mgx_batch* b, const mgx_launch_shape* in);
  * dividing chunk_steps, block size, persistent grid — with HIP events on the batch stream,
  * keeps the fastest, and records it in a process-wide cache keyed by (GPU architecture,
  * precision, per-class thruster counts and padded sizes, hold, chunk_steps). A cache hit
- * applies the stored shape without measuring. The batch's state and step counter are
- * restored afterwards (synchronous). */
+ * applies the stored shape without measuring. K is timed as mgx_batch_step launches it; a
+ * captured chunk whose stretches share launches (mgx_graph_capture) depends less on it. The
+ * batch's state and step counter are restored afterwards (synchronous). */
 mgx_status mgx_autotune(mgx_batch* b, const void* actions, int64_t n_rows, int64_t row0, int32_t hold,
                         int32_t chunk_steps, mgx_launch_shape* out);
 /* Cache persistence as plain text, one shape per line. */

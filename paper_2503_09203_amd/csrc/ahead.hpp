@@ -9,7 +9,7 @@
 // ahead of the first, without any exchange back, and hands each step's wrench over in LDS.
 // The arithmetic is the one-wave form's, value for value. 1000 steps in one launch: 437 -> 387
 // us for 65,536 environments (both waves on each SIMD), 407 -> 335 for 8,192; in double 567
-// -> 379 for 1,024. (The layout on the matrix cores, v_mfma_f32_4x4x1 with the layout's
+// -> 428 for 1,024 (builds with other register allocations of the same source 379 to 429). (The layout on the matrix cores, v_mfma_f32_4x4x1 with the layout's
 // columns broadcast, gives the same bits but holds the SIMD's other wave up: 466 us.)
 #pragma once
 #include <hip/hip_runtime.h>

@@ -248,7 +248,9 @@ struct StepArgs {
 };
 
 // The fewest steps per launch that the two-wave form takes: with fewer than one hand-over's
-// worth of steps after the first it has nothing to overlap.
+// worth of steps after the first it has nothing to overlap. (4-step launches are mostly 2 to 14%
+// faster so in float and 8 to 36% in double; of 57,000 to 65,536 environments the plain body in
+// float is up to 2% slower, and the payload body in double 2%.)
 constexpr int kAheadMinSteps = 4;
 
 // Whether a class launch of K steps runs two waves per tile (ahead.hpp): while the device has
