@@ -718,10 +718,10 @@ __global__ void __launch_bounds__(3 * kWave) k_rollout_bwd_split(AdjArgs A, Clas
     }
 
 // Whether every block of three waves finds its SIMDs at once. Beyond, the SIMDs fill with whole
-// tiles and the hand-over only adds work (forward of 65,536 x 64 168 against 149 us). Kernels in
-// double hold one wave per SIMD, and a second block of three does not fit the four SIMDs of a
-// compute unit: with more tiles than units, blocks would wait for others to end (forward of
-// 18,000 x 128 in double 30% slower than in two waves).
+// tiles and the hand-over only adds work (forward of 65,536 x 128 with eight thrusters 206
+// against 179 us). Kernels in double hold one wave per SIMD, and a second block of three does
+// not fit the four SIMDs of a compute unit: with more tiles than units, blocks would wait for
+// others to end (forward of 18,000 x 128 with six thrusters in double 180 us, 147 in two waves).
 template <typename T>
 static bool three_waves_fit(int64_t npad, int n_cu) {
     const int64_t tiles = npad / kWave;
@@ -737,7 +737,8 @@ hipError_t launch_rollout_fwd(const AdjArgs& A, const ClassT<T>& C, int m, bool 
     if (A.npad % kWave != 0) return hipErrorInvalidValue;
     const unsigned grid = (unsigned)(A.npad / kWave);
     // A rollout of one segment ends when that segment's tape is whole, which the wave that
-    // writes it starts later in three waves (16,384 x 16 22 us, 20 in two; x 48 43, 48 in two).
+    // writes it starts later in three waves (16,384 x 16 with six thrusters 23.0 us, 20.8 in
+    // two; x 48, two segments, 34.0, 37.8 in two).
     if (three_waves_fit<T>(A.npad, n_cu) && A.H > A.ckpt) {
         const unsigned block = 3 * kWave;
 #define KERNEL k_rollout_fwd_ahead
